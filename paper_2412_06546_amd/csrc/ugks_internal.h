@@ -46,24 +46,25 @@ template <int D> struct alignas(16) FaceGeo {
     double dr[D];  // right centroid (its periodic image) -> face centroid
 };
 
-// Interface equilibrium (Algorithm 1's third step).  For boundary faces only
-// (rho, U, lam) and pref are used: ghost Maxwellian (inflow), wall Maxwellian
-// with unit density (wall).
+// Interface record of a face (Algorithm 1's third step), as the velocity
+// loop uses it.  With c = u - U the peculiar velocity and
+// G = exp(-lam |c|^2), the time-integrated interface value of Eq.
+// fullSolution is
+//   h:  c0 f_s + c1 u . grad f_s + G P(c)
+//   b:  the same with G (bh P(c) + d0 + d1 . c)
+// where P(c) = k0 + k1 . c + c . k2 c + (k3 . c) |c|^2 gathers g0+ (Shakhov),
+// u . grad g0 and d_t g0 with their time integrals and g0's density: for a
+// Maxwellian all three are polynomials in c of at most third order, and h's
+// and b's differ in the constant and linear terms only.  Boundary faces:
+// c0, c1 free transport over the step, k0 = dt times the prefactor of the
+// Maxwellian that the incoming particles come from (a ghost, or the wall's
+// with unit density), all other coefficients zero.
 template <int D> struct alignas(16) FaceEq {
-    static constexpr int NW = D + 2;
-    double rho, U[D], lam;
-    double pref;          // rho (lam/pi)^{D/2}
-    double shk;           // 4 (1 - Pr) lam^2 / (5 rho)
-    double bh;            // M / (2 lam): B = bh H
-    double x4;            // M (M + 2) / (4 lam^2): int xi^4 g dxi = x4 H
-    double a[D][NW];      // spatial slopes of g0
-    double A[NW];         // time slope of g0
-    double q[D];          // interface heat flux
-    double c[5];          // time integrals of c1..c5 over the step
-    // the step and (dt / 2) dt for the free-transport and boundary fluxes; the
-    // sweep reads them with the face's other scalars, as the kernel argument
-    // kept live across the velocity loop costs scalar-register spill reloads
-    double dt, hdt2;
+    static constexpr int NK2 = D * (D + 1) / 2;
+    double U[D], lam;
+    double c0, c1;
+    double k0, k1[D], k2[NK2], k3[D];  // k2: c_a c_b, a <= b, row by row
+    double bh, d0, d1[D];              // 2D only (b); zero in 3D
 };
 
 struct Params {

@@ -346,39 +346,81 @@ __device__ __forceinline__ void shakhov(const double (&u)[D], const double (&U)[
     }
 }
 
-// Time-integrated interface value of h (and b) at velocity u (Eq. fullSolution
-// integrated over [0, dt]); val is the upwind reconstruction at the face,
-// ug = u . grad of the upwind cell, H0 the reduced Maxwellian g0 at u.
+// The equilibrium part of the time-integrated interface value (Eq.
+// fullSolution integrated over [0, dt]) at the peculiar velocity c of the
+// face's Maxwellian: G times a cubic in c (FaceEq).  18 FP64 instructions in
+// 3D where g0+, u . grad g0 and d_t g0 evaluated one by one took about 50.
 template <int D>
-__device__ __forceinline__ void interface_integral(const FaceEq<D> &e, const double (&u)[D], double u2, double H0,
-                                                   const double (&val)[Dim<D>::NC], const double (&ug)[Dim<D>::NC],
+__device__ __forceinline__ void face_equilibrium(const FaceEq<D> &e, const double (&c)[D], double c2, double G,
+                                                 double (&I)[Dim<D>::NC])
+{
+    double P = e.k0;
+    int t = 0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+        double r = fma(e.k3[a], c2, e.k1[a]);
+#pragma unroll
+        for (int b = a; b < D; ++b) r = fma(e.k2[t++], c[b], r);
+        P = fma(c[a], r, P);
+    }
+    I[0] = G * P;
+    if constexpr (Dim<D>::NC > 1) {
+        double B = fma(e.bh, P, e.d0);
+#pragma unroll
+        for (int a = 0; a < D; ++a) B = fma(e.d1[a], c[a], B);
+        I[Dim<D>::NC - 1] = G * B;
+    }
+}
+
+// The time-integrated interface value of h (and b) at velocity u through an
+// interior face: the upwind cell's values f and limited slopes gr, its
+// centroid-to-face vector, ug = u . gr; G the face's Gaussian at u.
+template <int D>
+__device__ __forceinline__ void interface_integral(const FaceEq<D> &e, const double (&u)[D], double G,
+                                                   const double (&f)[Dim<D>::NC], const double (&gr)[Dim<D>::NC][D],
+                                                   const double *dvec, const double (&ug)[Dim<D>::NC],
                                                    double (&I)[Dim<D>::NC])
 {
-    constexpr int M = Dim<D>::M, NW = D + 2;
-    double eqH, eqB;
-    shakhov<D>(u, e.U, e.lam, e.shk, e.q, e.bh, H0, eqH, eqB);
-    double Pd = 0.0, Ed = 0.0;
+    double c[D], c2 = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        double pa = e.a[d][0] + 0.5 * e.a[d][NW - 1] * u2;
-#pragma unroll
-        for (int c = 0; c < D; ++c) pa += e.a[d][1 + c] * u[c];
-        Pd += u[d] * pa;
-        Ed += u[d] * e.a[d][NW - 1];
+        c[d] = u[d] - e.U[d];
+        c2 = fma(c[d], c[d], c2);
     }
-    double PA = e.A[0] + 0.5 * e.A[NW - 1] * u2;
+    face_equilibrium<D>(e, c, c2, G, I);
 #pragma unroll
-    for (int c = 0; c < D; ++c) PA += e.A[1 + c] * u[c];
-    if constexpr (M > 0) {
-        const double B0 = e.bh * H0;
-        const double xi4 = e.x4 * H0;  // int xi^4 g0 dxi
-        const double gH = Pd * H0 + 0.5 * Ed * B0, gB = Pd * B0 + 0.5 * Ed * xi4;
-        const double tH = PA * H0 + 0.5 * e.A[NW - 1] * B0, tB = PA * B0 + 0.5 * e.A[NW - 1] * xi4;
-        I[0] = e.c[0] * val[0] + e.c[1] * ug[0] + e.c[2] * eqH + e.c[3] * gH + e.c[4] * tH;
-        I[1] = e.c[0] * val[1] + e.c[1] * ug[1] + e.c[2] * eqB + e.c[3] * gB + e.c[4] * tB;
-    } else {
-        const double gH = Pd * H0, tH = PA * H0;
-        I[0] = e.c[0] * val[0] + e.c[1] * ug[0] + e.c[2] * eqH + e.c[3] * gH + e.c[4] * tH;
+    for (int m = 0; m < Dim<D>::NC; ++m) {
+        double v = f[m];
+#pragma unroll
+        for (int d = 0; d < D; ++d) v = fma(gr[m][d], dvec[d], v);
+        I[m] = fma(e.c0, v, fma(e.c1, ug[m], I[m]));
+    }
+}
+
+// Free transport of the reconstruction over the step, out through a boundary face.
+template <int D>
+__device__ __forceinline__ void boundary_outgoing(const FaceEq<D> &e, const double (&f)[Dim<D>::NC],
+                                                  const double (&gr)[Dim<D>::NC][D], const double *dvec,
+                                                  const double (&ug)[Dim<D>::NC], double (&I)[Dim<D>::NC])
+{
+#pragma unroll
+    for (int m = 0; m < Dim<D>::NC; ++m) {
+        double v = f[m];
+#pragma unroll
+        for (int d = 0; d < D; ++d) v = fma(gr[m][d], dvec[d], v);
+        I[m] = fma(e.c1, ug[m], e.c0 * v);
+    }
+}
+
+// u . gr of every component
+template <int D>
+__device__ __forceinline__ void along(const double (&u)[D], const double (&gr)[Dim<D>::NC][D], double (&ug)[Dim<D>::NC])
+{
+#pragma unroll
+    for (int m = 0; m < Dim<D>::NC; ++m) {
+        ug[m] = 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) ug[m] = fma(u[d], gr[m][d], ug[m]);
     }
 }
 
@@ -577,68 +619,51 @@ __global__ __launch_bounds__(256) void k_cell_grad(Params p)
 // ------------------------------------------------------------------------
 // Algorithm 1, interface equilibrium state and time coefficients
 // ------------------------------------------------------------------------
-// Solve <psi (a . psi)>_{g} = Delta for a Maxwellian (rho-normalised
-// moments, N = 3 degrees of freedom), in closed form.
+// Slopes of a Maxwellian in its own frame: with c = u - U, a quantity
+// a . (1, c, (|c|^2 + |xi|^2) / 2) with <(1, c, ..) (a . (1, c, ..))>_g = Delta
+// for the rho-normalised moments of g (N = 3 degrees of freedom), s = 1 / (2 lam);
+// Dl holds Delta for (1, u, |u|^2 / 2 + |xi|^2 / 2), as a gradient of W / rho is given.
 template <int D>
-__device__ void slope_solve(const double (&U)[D], double lam, const double *Dl, double *a)
+__device__ __forceinline__ void slope_solve(const double (&U)[D], double s, const double *Dl, double (&a)[D + 2])
 {
     constexpr int NW = D + 2;
-    double U2 = 0.0, UR = 0.0, R[D];
+    double U2 = 0.0, Um = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        U2 += U[d] * U[d];
-        R[d] = Dl[1 + d] - U[d] * Dl[0];
-        UR += U[d] * R[d];
+        U2 = fma(U[d], U[d], U2);
+        Um = fma(U[d], Dl[1 + d], Um);
+        a[1 + d] = (Dl[1 + d] - U[d] * Dl[0]) / s;
     }
-    const double K2 = U2 + N_DOF / (2.0 * lam);
-    const double RE = 2.0 * Dl[NW - 1] - K2 * Dl[0];
-    const double aE = (4.0 * lam * lam / N_DOF) * (RE - 2.0 * UR);
-    double Ua = 0.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        a[1 + d] = 2.0 * lam * R[d] - U[d] * aE;
-        Ua += U[d] * a[1 + d];
-    }
-    a[NW - 1] = aE;
-    a[0] = Dl[0] - Ua - 0.5 * aE * K2;
+    const double De = Dl[NW - 1] - Um + 0.5 * U2 * Dl[0];
+    a[NW - 1] = (De - 0.5 * N_DOF * s * Dl[0]) / (0.5 * N_DOF * s * s);
+    a[0] = Dl[0] - 0.5 * N_DOF * s * a[NW - 1];
 }
 
-// -sum_d <psi u_d (a^d . psi)>_g  (Gaussian moments to fifth order)
+// Time slope from the compatibility condition <psi (u . grad g0 + d_t g0)> = 0
+// (Section 2.4), in the same frame: the right side
+// -sum_d <(1, c, ..) (U_d + c_d) (a^d . (1, c, ..))> by the Maxwellian's even
+// moments <c_i c_j> = s, <e> = N s / 2, <c_i c_j e> = (N + 2) s^2 / 2,
+// <e^2> = N (N + 2) s^2 / 4, then the same solve.
 template <int D>
-__device__ void compat_rhs(const double (&U)[D], double lam, const double (*a)[D + 2], double *r)
+__device__ __forceinline__ void time_slope(const double (&U)[D], double s, const double (&a)[D][D + 2],
+                                           double (&A)[D + 2])
 {
     constexpr int NW = D + 2, N = N_DOF;
-    const double s = 1.0 / (2.0 * lam);
-    double U2 = 0.0;
+    double r0 = 0.0, re = 0.0, rb[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) U2 += U[d] * U[d];
-    const double E = 0.5 * (U2 + N * s);
-    const double c4 = U2 + (N + 4) * s, c2 = s * (U2 + (N + 2) * s);
-    const double e2 = 0.25 * (U2 * U2 + 2.0 * (N + 4) * s * U2 + (N + 2) * (N + 4) * s * s);
-    for (int m = 0; m < NW; ++m) r[m] = 0.0;
+    for (int b = 0; b < D; ++b) rb[b] = -(s * a[b][0] + 0.5 * (N + 2) * s * s * a[b][NW - 1]);
+#pragma unroll
     for (int d = 0; d < D; ++d) {
-        const double *ad = a[d];
-        const double a0 = ad[0], aE = ad[NW - 1];
-        // row 0
-        double t = U[d] * a0 + U[d] * (E + s) * aE;
-        for (int c = 0; c < D; ++c) t += (U[c] * U[d] + (c == d ? s : 0.0)) * ad[1 + c];
-        r[0] -= t;
-        // momentum rows
-        for (int b = 0; b < D; ++b) {
-            double tb = (U[b] * U[d] + (b == d ? s : 0.0)) * a0;
-            for (int c = 0; c < D; ++c) {
-                double m3 = U[b] * U[c] * U[d] +
-                            s * ((c == d ? U[b] : 0.0) + (b == d ? U[c] : 0.0) + (b == c ? U[d] : 0.0));
-                tb += m3 * ad[1 + c];
-            }
-            tb += 0.5 * (U[b] * U[d] * c4 + (b == d ? c2 : 0.0)) * aE;
-            r[1 + b] -= tb;
-        }
-        // energy row
-        double te = U[d] * (E + s) * a0 + U[d] * e2 * aE;
-        for (int c = 0; c < D; ++c) te += 0.5 * (U[c] * U[d] * c4 + (c == d ? c2 : 0.0)) * ad[1 + c];
-        r[NW - 1] -= te;
+        r0 -= U[d] * (a[d][0] + 0.5 * N * s * a[d][NW - 1]) + s * a[d][1 + d];
+        re -= U[d] * (0.5 * N * s * a[d][0] + 0.25 * N * (N + 2) * s * s * a[d][NW - 1]) +
+              0.5 * (N + 2) * s * s * a[d][1 + d];
+#pragma unroll
+        for (int b = 0; b < D; ++b) rb[b] -= s * U[d] * a[d][1 + b];
     }
+#pragma unroll
+    for (int b = 0; b < D; ++b) A[1 + b] = rb[b] / s;
+    A[NW - 1] = (re - 0.5 * N * s * r0) / (0.5 * N * s * s);
+    A[0] = r0 - 0.5 * N * s * A[NW - 1];
 }
 
 __device__ void time_integrals(double dt, double tau, double *c)
@@ -684,8 +709,6 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
     if (f >= p.nf) return;
     const FaceGeo<D> &F = static_cast<const FaceGeo<D> *>(p.fgeo)[f];
     FaceEq<D> &e = static_cast<FaceEq<D> *>(p.feq)[f];
-    e.dt = p.dt;
-    e.hdt2 = 0.5 * p.dt * p.dt;
     if (F.bc != 0) {
         // boundary: store the Maxwellian the incoming particles come from
         double rho, U[D], lam;
@@ -700,13 +723,13 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
             for (int d = 0; d < D; ++d) U[d] = bp[1 + d];
             lam = 1.0 / bp[NW - 1];
         }
-        e.rho = rho;
+        // (the coefficients not written here are zero since creation)
         e.lam = lam;
         for (int d = 0; d < D; ++d) e.U[d] = U[d];
-        e.pref = rho * pow_lam_pi<D>(lam);
-        e.shk = 0.0;
+        e.c0 = p.dt;
+        e.c1 = -0.5 * p.dt * p.dt;
+        e.k0 = p.dt * rho * pow_lam_pi<D>(lam);
         e.bh = Dim<D>::M / (2.0 * lam);
-        e.x4 = 0.0;
         return;
     }
     // reconstructed states on both sides
@@ -746,27 +769,58 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
         for (int d = 0; d < D; ++d) W0[1 + d] += pr.rho * (m1 * F.n[d] + Ut[d] * m0);
         W0[NW - 1] += 0.5 * pr.rho * (m2 + (ut2 + (N_DOF - 1) / (2.0 * pr.lam)) * m0);
     }
-    Prim<D> p0 = to_prim<D>(W0);
-    e.rho = p0.rho;
-    e.lam = p0.lam;
-    for (int d = 0; d < D; ++d) e.U[d] = p0.U[d];
-    e.pref = p0.rho * pow_lam_pi<D>(p0.lam);
-    e.shk = 4.0 * (1.0 - p.Pr) * p0.lam * p0.lam / (5.0 * p0.rho);
-    e.bh = Dim<D>::M / (2.0 * p0.lam);
-    e.x4 = Dim<D>::M * (Dim<D>::M + 2) / (4.0 * p0.lam * p0.lam);
-    // spatial slopes from the averaged limited gradients
+    const Prim<D> p0 = to_prim<D>(W0);
+    const double s = 1.0 / (2.0 * p0.lam);
+    // spatial slopes from the averaged limited gradients, the time slope
+    double a[D][NW], A[NW], q[D], c[5];
+#pragma unroll
     for (int d = 0; d < D; ++d) {
         double Dl[NW];
+#pragma unroll
         for (int m = 0; m < NW; ++m)
             Dl[m] = 0.5 * (p.gW[((size_t)F.l * NW + m) * D + d] + p.gW[((size_t)F.r * NW + m) * D + d]) / p0.rho;
-        slope_solve<D>(p0.U, p0.lam, Dl, e.a[d]);
+        slope_solve<D>(p0.U, s, Dl, a[d]);
+        q[d] = 0.5 * (p.q[(size_t)F.l * D + d] + p.q[(size_t)F.r * D + d]);
     }
-    double rhs[NW];
-    compat_rhs<D>(p0.U, p0.lam, e.a, rhs);
-    slope_solve<D>(p0.U, p0.lam, rhs, e.A);
-    for (int d = 0; d < D; ++d) e.q[d] = 0.5 * (p.q[(size_t)F.l * D + d] + p.q[(size_t)F.r * D + d]);
-    const double tau0 = collision_time(p0.rho, p0.lam, p.mu_ref, p.omega);
-    time_integrals(p.dt, tau0, e.c);
+    time_slope<D>(p0.U, s, a, A);
+    time_integrals(p.dt, collision_time(p0.rho, p0.lam, p.mu_ref, p.omega), c);
+    // the cubic in c: c[2] (1 + Shakhov) + c[3] u . a + c[4] A.  Integrated
+    // over xi the energy moment (|c|^2 + |xi|^2) / 2 becomes
+    // (|c|^2 + M s) / 2 for h and (|c|^2 + (M + 2) s) / 2 for b = M s h.
+    constexpr int M = Dim<D>::M;
+    const double pref = p0.rho * pow_lam_pi<D>(p0.lam);
+    const double sh = c[2] * 4.0 * (1.0 - p.Pr) * p0.lam * p0.lam / (5.0 * p0.rho);  // Shakhov's factor
+    const double th = 0.5 * M * s;
+    double Ua0 = 0.0, UaE = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        Ua0 += p0.U[d] * a[d][0];
+        UaE += p0.U[d] * a[d][NW - 1];
+    }
+    const double e2 = c[3] * UaE + c[4] * A[NW - 1];  // factor of the energy moment
+    e.lam = p0.lam;
+    e.c0 = c[0];
+    e.c1 = c[1];
+    e.k0 = pref * (c[2] + c[3] * Ua0 + c[4] * A[0] + th * e2);
+    int t = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        e.U[d] = p0.U[d];
+        double lin = a[d][0] + th * a[d][NW - 1];
+#pragma unroll
+        for (int b = 0; b < D; ++b) lin += p0.U[b] * a[b][1 + d];
+        e.k1[d] = pref * (c[3] * lin + c[4] * A[1 + d] - sh * (2.0 + D) * q[d]);
+        e.k3[d] = pref * (0.5 * c[3] * a[d][NW - 1] + 2.0 * sh * p0.lam * q[d]);
+#pragma unroll
+        for (int b = d; b < D; ++b)
+            e.k2[t++] = pref * (b == d ? c[3] * a[d][1 + d] + 0.5 * e2 : c[3] * (a[d][1 + b] + a[b][1 + d]));
+    }
+    if constexpr (M > 0) {
+        e.bh = M * s;
+        e.d0 = e.bh * pref * s * e2;
+#pragma unroll
+        for (int d = 0; d < D; ++d) e.d1[d] = e.bh * pref * (c[3] * s * a[d][NW - 1] + 2.0 * sh * q[d]);
+    }
 }
 
 template <int D>
@@ -953,7 +1007,7 @@ __device__ __forceinline__ void wall_density(const Params &p, const CellGeo<D> &
                 wsum[2 * j] += wk * un * (dt * v - 0.5 * dt * dt * ug);
             } else {
                 const FaceEq<D> &e = fe[gi.face[j]];
-                wsum[2 * j + 1] += wk * un * dt * e.pref * gauss(j, kx, u, e.lam, e.U);
+                wsum[2 * j + 1] += wk * un * e.k0 * gauss(j, kx, u, e.lam, e.U);
             }
         }
     }
@@ -1070,7 +1124,7 @@ template <int D, typename FT, int BS, bool TENSOR, bool S1L, bool PF, bool CHUNK
 __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__restrict__ fin, FT *__restrict__ fout,
                                            int c0 = 0, int cn = 0, int prev0 = 0, int prevn = 0, int ichunk = 0)
 {
-    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, M = Dim<D>::M, NW = D + 2;
+    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NW = D + 2;
     constexpr int NT = MF + 1;  // Gaussian tables: one per face slot, one for the cell
     extern __shared__ double smem[];
     if (i >= p.nc) return;
@@ -1181,7 +1235,7 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
                     wsum[2 * j] += wk * un * (dt * v - 0.5 * dt * dt * ug);
                 } else {
                     const FaceEq<D> &e = fe[gi.face[j]];
-                    wsum[2 * j + 1] += wk * un * dt * e.pref * gauss(j, kx, u, e.lam, e.U);
+                    wsum[2 * j + 1] += wk * un * e.k0 * gauss(j, kx, u, e.lam, e.U);
                 }
             }
         }
@@ -1218,7 +1272,8 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
         double fi[NC], gri[NC][D];
         if constexpr (PF) slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
         else limited_slope<D, FT>(gi, i, fin, nv, k, p.limiter, fi, gri);
-        double out[NC];
+        double out[NC], ugi[NC];
+        along<D>(u, gri, ugi);
 #pragma unroll
         for (int c = 0; c < NC; ++c) out[c] = 0.0;
 #pragma unroll
@@ -1233,54 +1288,23 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
             double I[NC];
             if (F.bc == 0) {
                 const bool self_up = (un > 0.0) == (gi.side[j] == 0);
-                double val[NC], ug[NC];
+                const double G = gauss(j, kx, u, e.lam, e.U);
                 if (self_up) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        val[c] = fi[c];
-                        ug[c] = 0.0;
-#pragma unroll
-                        for (int d = 0; d < D; ++d) {
-                            val[c] += gri[c][d] * gi.dvec[j][d];
-                            ug[c] += u[d] * gri[c][d];
-                        }
-                    }
+                    interface_integral<D>(e, u, G, fi, gri, gi.dvec[j], ugi, I);
                 } else {
                     const int n = gi.nb[j];
                     const CellGeo<D> &gn = cg[n];
-                    const int bj = gi.back[j];
-                    double fn[NC], grn[NC][D];
+                    double fn[NC], grn[NC][D], ug[NC];
                     limited_slope<D, FT>(gn, n, fin, nv, k, p.limiter, fn, grn);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        val[c] = fn[c];
-                        ug[c] = 0.0;
-#pragma unroll
-                        for (int d = 0; d < D; ++d) {
-                            val[c] += grn[c][d] * gn.dvec[bj][d];
-                            ug[c] += u[d] * grn[c][d];
-                        }
-                    }
+                    along<D>(u, grn, ug);
+                    interface_integral<D>(e, u, G, fn, grn, gn.dvec[gi.back[j]], ug, I);
                 }
-                const double H0 = e.pref * gauss(j, kx, u, e.lam, e.U);
-                interface_integral<D>(e, u, u2, H0, val, ug, I);
             } else if (un > 0.0) {
-                // outgoing through a wall or far-field face: free transport
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    double v = fi[c], ug = 0.0;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        v += gri[c][d] * gi.dvec[j][d];
-                        ug += u[d] * gri[c][d];
-                    }
-                    I[c] = e.dt * v - e.hdt2 * ug;
-                }
+                boundary_outgoing<D>(e, fi, gri, gi.dvec[j], ugi, I);
             } else {
                 // incoming from the wall (density rho_w) or the ghost Maxwellian
-                const double H = (F.bc == 3 ? rho_w[j] : 1.0) * e.pref * gauss(j, kx, u, e.lam, e.U);
-                I[0] = e.dt * H;
-                if constexpr (NC > 1) I[1] = e.dt * e.bh * H;
+                I[0] = (F.bc == 3 ? rho_w[j] : 1.0) * e.k0 * gauss(j, kx, u, e.lam, e.U);
+                if constexpr (NC > 1) I[1] = e.bh * I[0];
             }
             const double sa = (gi.side[j] ? -F.area : F.area) * un;
 #pragma unroll
@@ -1754,7 +1778,7 @@ __device__ __forceinline__ void push_wall(const Params &p, const CellGeo<D> &gi,
 #pragma unroll
                 for (int m = 0; m < NW; ++m) s[m] += mm[m];
             } else {
-                const double H = dt * e.pref * gauss(j, (TENSOR ? (unsigned)p.kidx[k] : 0u), u, e.lam, e.U);
+                const double H = e.k0 * gauss(j, (TENSOR ? (unsigned)p.kidx[k] : 0u), u, e.lam, e.U);
                 I[0] = H;
                 if constexpr (NC > 1) I[1] = e.bh * H;
                 s[2 * NW + 1] = fma(wk * un, I[0], s[2 * NW + 1]);
@@ -1829,7 +1853,8 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
         const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
         double fi[NC], gri[NC][D];
         slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
-        double out[NC];
+        double out[NC], ug[NC];
+        along<D>(u, gri, ug);
 #pragma unroll
         for (int c = 0; c < NC; ++c) out[c] = 0.0;
         // faces one at a time (not unrolled: their records are read with
@@ -1847,19 +1872,8 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
             if (F.bc == 0) {
                 if (!(uo > 0.0)) continue;  // the neighbour is upwind: it adds this flux
                 AT *an = acc + (size_t)gi.nb[j] * NC * accv;
-                double val[NC], ug[NC], I[NC];
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    val[c] = fi[c];
-                    ug[c] = 0.0;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        val[c] = fma(gri[c][d], gi.dvec[j][d], val[c]);
-                        ug[c] = fma(u[d], gri[c][d], ug[c]);
-                    }
-                }
-                const double H0 = e.pref * gauss(j, kx, u, e.lam, e.U);
-                interface_integral<D>(e, u, u2, H0, val, ug, I);
+                double I[NC];
+                interface_integral<D>(e, u, gauss(j, kx, u, e.lam, e.U), fi, gri, gi.dvec[j], ug, I);
                 const double sa = F.area * uo;
                 const double vn_inv = gi.nb_inv_vol[j];
 #pragma unroll
@@ -1875,22 +1889,11 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
             } else {
                 double I[NC];
                 if (un > 0.0) {
-                    // outgoing through a wall or far-field face: free transport
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        double v = fi[c], ug = 0.0;
-#pragma unroll
-                        for (int d = 0; d < D; ++d) {
-                            v = fma(gri[c][d], gi.dvec[j][d], v);
-                            ug = fma(u[d], gri[c][d], ug);
-                        }
-                        I[c] = e.dt * v - e.hdt2 * ug;
-                    }
+                    boundary_outgoing<D>(e, fi, gri, gi.dvec[j], ug, I);
                 } else {
                     // incoming from the wall (density rho_w) or the ghost Maxwellian
-                    const double H = (F.bc == 3 ? rho_w[j] : 1.0) * e.pref * gauss(j, kx, u, e.lam, e.U);
-                    I[0] = e.dt * H;
-                    if constexpr (NC > 1) I[1] = e.dt * e.bh * H;
+                    I[0] = (F.bc == 3 ? rho_w[j] : 1.0) * e.k0 * gauss(j, kx, u, e.lam, e.U);
+                    if constexpr (NC > 1) I[1] = e.bh * I[0];
                 }
                 const double sa = F.area * un;  // a boundary cell is the face's left cell
 #pragma unroll
@@ -2227,9 +2230,8 @@ __global__ __launch_bounds__(BS) void k_wall_flux(Params p, const FT *__restrict
                 const double cd = u[d] - e.U[d];
                 c2 += cd * cd;
             }
-            const double H = e.pref * exp(-e.lam * c2);
-            I[0] = dt * H;
-            I[1] = NC > 1 ? dt * e.bh * H : 0.0;
+            I[0] = e.k0 * exp(-e.lam * c2);
+            I[1] = NC > 1 ? e.bh * I[0] : 0.0;
             off = NW;
         }
         const double a = wk * un;
