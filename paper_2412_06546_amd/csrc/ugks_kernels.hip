@@ -1961,13 +1961,17 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(D == 3 ? 6 :
 
 // Velocity splits of a colour launch: a class of n cells gets up to enough
 // workgroups to fill the chip (kPushFill), each with a share of the kn
-// velocities that is a multiple of the workgroup size and at least
-// kPushMinIters iterations long (every workgroup repeats the cell's set-up).
-constexpr int kPushFill = 8192, kPushMinIters = 4;
+// velocities that is a multiple of the workgroup size.  A class too small to
+// fill the chip is bound by the length of one workgroup, not by the cell
+// set-up that every workgroup repeats, so a share may be a single iteration:
+// with at least four iterations a share, a colour launch of a 2,197-cell
+// channel (1,331 velocities) took 24.2 us and now takes 13.0, one of a
+// 4,096-cell box with 2,145 scattered velocities 32.8 and now 23.3.
+constexpr int kPushFill = 8192;
 inline int push_ksplit(int n, int kn, int bs)
 {
     const int iters = (kn + bs - 1) / bs;  // velocity iterations of one workgroup
-    const int split = std::max(1, std::min(iters / kPushMinIters, (kPushFill + n - 1) / n));
+    const int split = std::max(1, std::min(iters, (kPushFill + n - 1) / n));
     const int per = (iters + split - 1) / split;
     return per * bs;
 }
