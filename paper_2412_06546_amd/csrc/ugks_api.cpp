@@ -131,8 +131,9 @@ void upload(void *dst, const void *src, size_t bytes, hipStream_t s)
 // for Cartesian grids, and equally for octree-refined or ball-restricted
 // sets, whose points share few coordinate values per axis.  Returns 1 with
 // the axes (the sorted distinct values, x then y [then z]), their counts and
-// every velocity's packed axis indices (a | b << 10 | c << 20), when every
-// axis has at most 1023 distinct values.
+// every velocity's positions in a table of the axes one after another, packed
+// (a | b << 10 | c << 20), when the axes have at most 1023 distinct values in
+// all.
 int detect_tensor(int D, int nv, const double *u, int n1d[3], std::vector<double> &axes, std::vector<int> &kidx)
 {
     std::vector<double> vals[3];
@@ -143,17 +144,19 @@ int detect_tensor(int D, int nv, const double *u, int n1d[3], std::vector<double
         vals[d].erase(std::unique(vals[d].begin(), vals[d].end()), vals[d].end());
         if (vals[d].size() > 1023) return 0;
     }
+    if (vals[0].size() + vals[1].size() + vals[2].size() > 1023) return 0;
     axes.clear();
     for (int d = 0; d < 3; ++d) {
         n1d[d] = d < D ? (int)vals[d].size() : 0;
         if (d < D) axes.insert(axes.end(), vals[d].begin(), vals[d].end());
     }
     kidx.assign(nv, 0);
+    const int start[3] = {0, n1d[0], n1d[0] + n1d[1]};
     for (int k = 0; k < nv; ++k)
         for (int d = 0; d < D; ++d) {
             const double x = u[(size_t)k * D + d];
             const int a = (int)(std::lower_bound(vals[d].begin(), vals[d].end(), x) - vals[d].begin());
-            kidx[k] |= a << (10 * d);
+            kidx[k] |= (start[d] + a) << (10 * d);
         }
     return 1;
 }

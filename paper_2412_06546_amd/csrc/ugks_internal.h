@@ -77,8 +77,9 @@ struct Params {
     void *feq;
     const double *u;   // [dim][nv] (structure of arrays)
     const double *w;   // [nv]
-    // Cartesian velocity grids: 1D axes [nx | ny | nz] and per-velocity axis
-    // indices packed as a | b << 10 | c << 20; ntab = nx + ny + nz, 0 otherwise
+    // Cartesian velocity grids: 1D axes [nx | ny | nz] and per-velocity
+    // positions in that list packed as a | b << 10 | c << 20; ntab = nx + ny +
+    // nz, 0 otherwise
     const double *u1d;
     const int *kidx;
     int n1d[3];

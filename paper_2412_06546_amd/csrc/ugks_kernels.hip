@@ -325,17 +325,13 @@ __device__ __forceinline__ void limited_slope(const CellGeo<D> &g, int c, const 
 // H+ = shk (c.q)(2 lam c^2 - 2 - D) H, B = M/(2 lam) H,
 // B+ = shk (c.q)(2 lam c^2 - D) B, with shk = 4 (1 - Pr) lam^2 / (5 rho).
 template <int D>
-__device__ __forceinline__ void shakhov(const double (&u)[D], const double (&U)[D], double lam, double shk,
-                                        const double (&q)[D], double bh, double H, double &fh, double &fb)
+__device__ __forceinline__ void shakhov_at(const double (&c)[D], double c2, double lam, double shk, const double (&q)[D],
+                                           double bh, double H, double &fh, double &fb)
 {
     constexpr int M = Dim<D>::M;
-    double c2 = 0.0, cq = 0.0;
+    double cq = 0.0;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const double c = u[d] - U[d];
-        c2 = fma(c, c, c2);
-        cq = fma(c, q[d], cq);
-    }
+    for (int d = 0; d < D; ++d) cq = fma(c[d], q[d], cq);
     const double s = shk * cq, l2 = 2.0 * lam * c2;
     fh = fma(s * (l2 - 2.0 - D), H, H);
     if constexpr (M > 0) {
@@ -344,6 +340,27 @@ __device__ __forceinline__ void shakhov(const double (&u)[D], const double (&U)[
     } else {
         fb = 0.0;
     }
+}
+
+// the peculiar velocity about U and its square
+template <int D>
+__device__ __forceinline__ void peculiar(const double (&u)[D], const double *U, double (&c)[D], double &c2)
+{
+    c2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        c[d] = u[d] - U[d];
+        c2 = fma(c[d], c[d], c2);
+    }
+}
+
+template <int D>
+__device__ __forceinline__ void shakhov(const double (&u)[D], const double (&U)[D], double lam, double shk,
+                                        const double (&q)[D], double bh, double H, double &fh, double &fb)
+{
+    double c[D], c2;
+    peculiar<D>(u, U, c, c2);
+    shakhov_at<D>(c, c2, lam, shk, q, bh, H, fh, fb);
 }
 
 // The equilibrium part of the time-integrated interface value (Eq.
@@ -381,12 +398,8 @@ __device__ __forceinline__ void interface_integral(const FaceEq<D> &e, const dou
                                                    const double *dvec, const double (&ug)[Dim<D>::NC],
                                                    double (&I)[Dim<D>::NC])
 {
-    double c[D], c2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        c[d] = u[d] - e.U[d];
-        c2 = fma(c[d], c[d], c2);
-    }
+    double c[D], c2;
+    peculiar<D>(u, e.U, c, c2);
     face_equilibrium<D>(e, c, c2, G, I);
 #pragma unroll
     for (int m = 0; m < Dim<D>::NC; ++m) {
@@ -838,14 +851,13 @@ __global__ __launch_bounds__(128) void k_face_eq(Params p)
 template <int D, bool TENSOR> struct Gauss {
     const double *tab;  // LDS tables, ntab doubles each
     int ntab;
-    int off1, off2;     // start of the y and z axes inside a table
     __device__ __forceinline__ double operator()(int t, unsigned kx, const double (&u)[D], double lam,
                                                  const double *U) const
     {
         if constexpr (TENSOR) {
             const double *tb = tab + t * ntab;
-            double g = tb[kx & 1023u] * tb[off1 + ((kx >> 10) & 1023u)];
-            if constexpr (D == 3) g *= tb[off2 + (kx >> 20)];
+            double g = tb[kx & 1023u] * tb[kx >> 10 & 1023u];
+            if constexpr (D == 3) g *= tb[kx >> 20];
             return g;
         } else {
             double c2 = 0.0;
@@ -1137,7 +1149,7 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
     const double dt = p.dt, Pr = p.Pr;
     const int ntab = TENSOR ? p.ntab : 0;
     double *red = smem + NT * ntab;
-    const Gauss<D, TENSOR> gauss{smem, ntab, p.n1d[0], p.n1d[0] + p.n1d[1]};
+    const Gauss<D, TENSOR> gauss{smem, ntab};
     const size_t base = (size_t)i * NC * nv;
     constexpr int NRED = (NW > 2 * MF) ? NW : 2 * MF;
     // stage-1 values: LDS, f_out, or (chunk mode) the cell's ring, as
@@ -1444,7 +1456,7 @@ __global__ __launch_bounds__(BS) void k_wall_density(Params p, const FT *__restr
     const CellStep<D> cs = cell_step<D>(p, i);
     if constexpr (TENSOR) fill_tables<D, BS>(p, gi, cs.pn, smem);
     __syncthreads();
-    const Gauss<D, TENSOR> gauss{smem, ntab, p.n1d[0], p.n1d[0] + p.n1d[1]};
+    const Gauss<D, TENSOR> gauss{smem, ntab};
     double rho_w[MF];
     wall_density<D, FT, BS, TENSOR>(p, gi, i, f, gauss, smem + NT * ntab, rho_w);
     if (threadIdx.x == 0)
@@ -1491,7 +1503,7 @@ __global__ __launch_bounds__(BS) void k_sweep_finish(Params p, FT *__restrict__ 
         for (int m = 0; m < NW; ++m) mom[m] = 0.0;
     __syncthreads();
     constexpr int NT = Dim<D>::MF + 1;
-    const Gauss<D, TENSOR> gauss{smem, ntab, p.n1d[0], p.n1d[0] + p.n1d[1]};
+    const Gauss<D, TENSOR> gauss{smem, ntab};
     finish_cell<D, FT, BS, TENSOR>(p, i, cs, mom, fc, smem + NT * ntab, smem, gauss, f);
 }
 
@@ -1603,37 +1615,12 @@ __device__ __forceinline__ void velocity(const Params &p, int k, double (&u)[D],
     }
 }
 
-// Sum over the 64 lanes of a wavefront.  Every lane ends with the same
-// bits: each butterfly step adds the same two values in both partner lanes.
-__device__ __forceinline__ double wave_sum(double x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-// The cell's own Gaussian factor table for (U, lam), filled by one
-// wavefront into its own LDS region (ntab doubles), and a lookup in it.
-template <int D>
-__device__ __forceinline__ void fill_wave_table(const Params &p, const double (&U)[D], double lam, double *tb, int lane)
-{
-    const double U0 = U[0], U1 = U[1], U2 = U[D - 1];
-    for (int idx = lane; idx < p.ntab; idx += 64) {
-        const int ax = idx < p.n1d[0] ? 0 : (idx < p.n1d[0] + p.n1d[1] ? 1 : 2);
-        const double Ud = ax == 0 ? U0 : (ax == 1 ? U1 : U2);
-        const double c = p.u1d[idx] - Ud;
-        tb[idx] = exp(-lam * c * c);
-    }
-    // the lanes' LDS writes before any lane of the wavefront reads them
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
+// A lookup in a cell's own table of Gaussian factors.
 template <int D>
 __device__ __forceinline__ double wave_table_gauss(const Params &p, const double *tb, unsigned kx)
 {
-    double g = tb[kx & 1023u] * tb[p.n1d[0] + ((kx >> 10) & 1023u)];
-    if constexpr (D == 3) g *= tb[p.n1d[0] + p.n1d[1] + (kx >> 20)];
+    double g = tb[kx & 1023u] * tb[kx >> 10 & 1023u];
+    if constexpr (D == 3) g *= tb[kx >> 20];
     return g;
 }
 template <int D, bool TENSOR>
@@ -1651,76 +1638,6 @@ __device__ __forceinline__ double own_gauss(const Params &p, const double *tb, u
         }
         return exp(-lam * c2);
     }
-}
-
-// The per-cell streaming kernels of the push sweep run one wavefront per
-// cell (four cells per workgroup, consecutive): the reductions over a
-// cell's velocities are lane butterflies, with no workgroup barrier, so
-// that each wavefront streams its slab without waiting for others.
-constexpr int kPushCellsPerGroup = 4;
-
-// Stage-1 base of cell i and its moments: acc = f + (dt / 2 tau)(f+ - f)
-// from f^n, W^n, q^n (after a start, a restart or a step of another kind).
-// V2: velocities in pairs (even velocity count).  Same lane order and
-// arithmetic as the final kernel's second pass, so both give the same bits.
-template <int D, typename FT, bool TENSOR, bool V2>
-__global__ __launch_bounds__(256) void k_push_base(Params p, const FT *__restrict__ fin, typename AccOf<FT>::T *__restrict__ acc)
-{
-    using AT = typename AccOf<FT>::T;
-    constexpr int NC = Dim<D>::NC, NW = D + 2, VW = V2 ? 2 : 1;
-    extern __shared__ double smem[];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int i = kPushCellsPerGroup * xcd_cell(blockIdx.x) + wv;
-    if (i >= p.nc) return;
-    const int nv = p.nv;
-    const CellStep<D> cs = cell_step<D>(p, i);
-    double *tb = smem + (size_t)wv * (TENSOR ? p.ntab : 0);
-    if constexpr (TENSOR) fill_wave_table<D>(p, cs.pn.U, cs.pn.lam, tb, lane);
-    const size_t base = (size_t)i * NC * nv;
-    double mom[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mom[m] = 0.0;
-#pragma unroll 4
-    for (int k0 = VW * lane; k0 < nv; k0 += VW * 64) {
-        double f[VW][2];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (V2)
-                load2<FT>(fin + base + (size_t)c * nv + k0, f[0][c], f[1][c]);
-            else
-                f[0][c] = to_f64(fin[base + (size_t)c * nv + k0]);
-        }
-        AT sv[VW][2];
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const int k = k0 + e;
-            double u[D], u2;
-            velocity<D>(p, k, u, u2);
-            const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-            double fp[2];
-            const double H = cs.pref_n * own_gauss<D, TENSOR>(p, tb, kx, u, cs.pn.lam, cs.pn.U);
-            shakhov<D>(u, cs.pn.U, cs.pn.lam, cs.shk_n, cs.qn, cs.bh_n, H, fp[0], fp[1]);
-            double bv[2] = {0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                sv[e][c] = from_f64<AT>(fma(cs.hdt_tau, fp[c] - f[e][c], f[e][c]));
-                bv[c] = to_f64(sv[e][c]);
-            }
-            add_moments<D>(mom, p.w[k], u, u2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (V2)
-                store2<AT>(acc + base + (size_t)c * nv + k0, sv[0][c], sv[1][c]);
-            else
-                acc[base + (size_t)c * nv + k0] = sv[0][c];
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mom[m] = wave_sum(mom[m]);
-    if (lane == 0)
-#pragma unroll
-        for (int m = 0; m < NW; ++m) p.mom_part[(size_t)i * NW + m] = mom[m];
 }
 
 // Wall faces of cell i (Section 2.5): per wall face, the incident particles'
@@ -1812,7 +1729,7 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
                                           typename AccOf<FT>::T *__restrict__ acc, int k0, int kn, int accv)
 {
     using AT = typename AccOf<FT>::T;
-    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NT = MF + 1;
+    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF;
     extern __shared__ double smem[];
     const int tid = threadIdx.x;
     const CellGeo<D> &gi = static_cast<const CellGeo<D> *>(p.cgeo)[i];
@@ -1821,7 +1738,7 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
     const int nv = p.nv, nf = gi.nf, ntab = TENSOR ? p.ntab : 0;
     if constexpr (TENSOR) fill_tables<D, BS>(p, gi, to_prim<D>(p.W + (size_t)i * (D + 2)), smem);
     __syncthreads();
-    const Gauss<D, TENSOR> gauss{smem, ntab, p.n1d[0], p.n1d[0] + p.n1d[1]};
+    const Gauss<D, TENSOR> gauss{smem, ntab};
     // wall densities of this cell's wall faces, from the step's wall kernel
     const double *rho_w = p.rho_w + (size_t)i * MF;
 
@@ -1923,7 +1840,7 @@ __global__ __launch_bounds__(BS) void k_push_wall(Params p, const FT *__restrict
     const CellStep<D> cs = cell_step<D>(p, i);
     if constexpr (TENSOR) fill_tables<D, BS>(p, gi, cs.pn, smem);
     __syncthreads();
-    const Gauss<D, TENSOR> gauss{smem, ntab, p.n1d[0], p.n1d[0] + p.n1d[1]};
+    const Gauss<D, TENSOR> gauss{smem, ntab};
     double rho_w[MF];
     push_wall<D, FT, BS, TENSOR>(p, gi, i, fin, gauss, smem + NT * ntab, rho_w);
     if (threadIdx.x == 0)
@@ -1976,204 +1893,9 @@ inline int push_ksplit(int n, int kn, int bs)
     return per * bs;
 }
 
-// After the last colour: W^{n+1}, tau^{n+1}, q^{n+1}, stage 2 into f and the
-// next step's base into the accumulator; one wavefront per cell.
-//   pass 1: moments of the stage-1 values h (and b) about U^n -- orders 0 to
-//           3 of h, 0 and 1 of b -- in one sweep of the slab;
-//   macro:  mass, momentum and energy from them -> W^{n+1}, tau^{n+1}; the
-//           heat flux about U^{n+1} from the same moments, re-centred by
-//           delta = U^{n+1} - U^n (exact algebra: the third-order moment of
-//           (c - delta) expanded in delta), so no second pass is needed;
-//   pass 2: stage 2 (Eq. microS2) into f, the base into acc (re-reading the
-//           slab, which the cell's wavefront has just streamed through L2).
-// V2: velocities in pairs, in the order of the base kernel.
 template <int D> constexpr int sym_index(int a, int b)
 {
     return a <= b ? a * D - a * (a - 1) / 2 + (b - a) : b * D - b * (b - 1) / 2 + (a - b);
-}
-
-template <int D, typename FT, bool TENSOR, bool V2>
-__global__ __launch_bounds__(256) void k_push_final(Params p, FT *__restrict__ fout, typename AccOf<FT>::T *__restrict__ acc)
-{
-    using AT = typename AccOf<FT>::T;
-    constexpr int NC = Dim<D>::NC, NW = D + 2, VW = V2 ? 2 : 1, NM = D * (D + 1) / 2;
-    extern __shared__ double smem[];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int i = kPushCellsPerGroup * xcd_cell(blockIdx.x) + wv;
-    if (i >= p.nc) return;
-    const int nv = p.nv;
-    const double dt = p.dt, Pr = p.Pr;
-    const size_t base = (size_t)i * NC * nv;
-    double Wn[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) Wn[m] = p.W[(size_t)i * NW + m];
-    const Prim<D> pn = to_prim<D>(Wn);
-
-    // pass 1
-    double m0 = 0.0, m1[D], m2[NM], m3[D], b0 = 0.0, b1[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) m1[d] = m3[d] = b1[d] = 0.0;
-#pragma unroll
-    for (int t = 0; t < NM; ++t) m2[t] = 0.0;
-#pragma unroll 4
-    for (int k0 = VW * lane; k0 < nv; k0 += VW * 64) {
-        double v[VW][2];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (V2)
-                load2<AT>(acc + base + (size_t)c * nv + k0, v[0][c], v[1][c]);
-            else
-                v[0][c] = to_f64(acc[base + (size_t)c * nv + k0]);
-        }
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const int k = k0 + e;
-            const double w = p.w[k];
-            double c[D], c2 = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                c[d] = p.u[d * nv + k] - pn.U[d];
-                c2 = fma(c[d], c[d], c2);
-            }
-            const double wh = w * v[e][0];
-            m0 += wh;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const double whc = wh * c[a];
-                m1[a] += whc;
-                m3[a] = fma(whc, c2, m3[a]);
-#pragma unroll
-                for (int bb = a; bb < D; ++bb) m2[sym_index<D>(a, bb)] = fma(whc, c[bb], m2[sym_index<D>(a, bb)]);
-            }
-            if constexpr (NC > 1) {
-                const double wb = w * v[e][NC - 1];
-                b0 += wb;
-#pragma unroll
-                for (int a = 0; a < D; ++a) b1[a] = fma(wb, c[a], b1[a]);
-            }
-        }
-    }
-    m0 = wave_sum(m0);
-    b0 = wave_sum(b0);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        m1[d] = wave_sum(m1[d]);
-        m3[d] = wave_sum(m3[d]);
-        b1[d] = wave_sum(b1[d]);
-    }
-#pragma unroll
-    for (int t = 0; t < NM; ++t) m2[t] = wave_sum(m2[t]);
-
-    // macro: mass, momentum, energy of the stage-1 values
-    double mom[NW], trm2 = 0.0, um1 = 0.0, uu = 0.0;
-    mom[0] = m0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        mom[1 + a] = fma(pn.U[a], m0, m1[a]);
-        trm2 += m2[sym_index<D>(a, a)];
-        um1 = fma(pn.U[a], m1[a], um1);
-        uu = fma(pn.U[a], pn.U[a], uu);
-    }
-    mom[D + 1] = 0.5 * (trm2 + 2.0 * um1 + uu * m0 + b0);
-    double W1[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) W1[m] = Wn[m] + (mom[m] - p.mom_part[(size_t)i * NW + m]);
-    const Prim<D> p1 = to_prim<D>(W1);
-    const double tau1 = collision_time(p1.rho, p1.lam, p.mu_ref, p.omega);
-    // heat flux about U^{n+1}: sum w (c' |c'|^2 h + c' b) / 2 with c' = c - delta
-    double dl[D], d2 = 0.0, m1d = 0.0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        dl[a] = p1.U[a] - pn.U[a];
-        d2 = fma(dl[a], dl[a], d2);
-        m1d = fma(m1[a], dl[a], m1d);
-    }
-    double q1[D];
-    const double qden = 1.0 + Pr * dt / (2.0 * tau1);
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        double m2d = 0.0;
-#pragma unroll
-        for (int bb = 0; bb < D; ++bb) m2d = fma(m2[sym_index<D>(a, bb)], dl[bb], m2d);
-        const double qa = m3[a] - 2.0 * m2d + d2 * m1[a] - dl[a] * trm2 + 2.0 * dl[a] * m1d - dl[a] * d2 * m0 + b1[a] -
-                          dl[a] * b0;
-        q1[a] = 0.5 * qa / qden;
-    }
-
-    double *tb = smem + (size_t)wv * (TENSOR ? p.ntab : 0);
-    if constexpr (TENSOR) fill_wave_table<D>(p, p1.U, p1.lam, tb, lane);
-
-    // pass 2: stage 2 into f, the next step's base into acc
-    const double pref_1 = p1.rho * pow_lam_pi<D>(p1.lam);
-    const double shk_1 = 4.0 * (1.0 - Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
-    const double a1 = 0.5 * dt / tau1, inv1 = 1.0 / (1.0 + a1);
-    const double bh_1 = Dim<D>::M / (2.0 * p1.lam);
-    double mb[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mb[m] = 0.0;
-#pragma unroll 2
-    for (int k0 = VW * lane; k0 < nv; k0 += VW * 64) {
-        double sv[VW][2];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (V2)
-                load2<AT>(acc + base + (size_t)c * nv + k0, sv[0][c], sv[1][c]);
-            else
-                sv[0][c] = to_f64(acc[base + (size_t)c * nv + k0]);
-        }
-        FT fo[VW][2];
-        AT bo[VW][2];
-#pragma unroll
-        for (int e = 0; e < VW; ++e) {
-            const int k = k0 + e;
-            double u[D], u2;
-            velocity<D>(p, k, u, u2);
-            const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-            double fp[2];
-            const double H = pref_1 * own_gauss<D, TENSOR>(p, tb, kx, u, p1.lam, p1.U);
-            shakhov<D>(u, p1.U, p1.lam, shk_1, q1, bh_1, H, fp[0], fp[1]);
-            double bv[2] = {0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                fo[e][c] = from_f64<FT>((sv[e][c] + a1 * fp[c]) * inv1);
-                // the base from f^{n+1} as stored (bitwise what the base
-                // kernel computes from it after a restart)
-                const double fd = opaque(to_f64(fo[e][c]));
-                bo[e][c] = from_f64<AT>(fma(a1, fp[c] - fd, fd));
-                bv[c] = to_f64(bo[e][c]);
-            }
-            add_moments<D>(mb, p.w[k], u, u2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            if constexpr (V2) {
-                store2<FT>(fout + base + (size_t)c * nv + k0, fo[0][c], fo[1][c]);
-                store2<AT>(acc + base + (size_t)c * nv + k0, bo[0][c], bo[1][c]);
-            } else {
-                fout[base + (size_t)c * nv + k0] = fo[0][c];
-                acc[base + (size_t)c * nv + k0] = bo[0][c];
-            }
-        }
-    }
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mb[m] = wave_sum(mb[m]);
-    if (lane == 0) {
-        bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
-#pragma unroll
-        for (int m = 0; m < NW; ++m) {
-            ok = ok && isfinite(W1[m]);
-            p.W[(size_t)i * NW + m] = W1[m];
-            const double dw = W1[m] - Wn[m];
-            p.dW2[(size_t)i * NW + m] = dw * dw;
-            p.mom_part[(size_t)i * NW + m] = mb[m];
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d) p.q[(size_t)i * D + d] = q1[d];
-        if (!ok) {
-            atomicOr(p.err, 1);
-            atomicMin(p.err + 1, i);
-        }
-    }
 }
 
 // ------------------------------------------------------------------------
@@ -2524,242 +2246,54 @@ hipError_t launch_sweep(const Params &p, const void *fi, void *fo, hipStream_t s
 }
 
 // ------------------------------------------------------------------------
-// Register-resident form of the push sweep's per-cell kernels, for slabs of
-// at most NPT velocities per thread (one 256-thread workgroup per cell;
-// thread t holds velocities t, t + 256, ...): the final kernel loads the
-// whole stage-1 slab into registers in one go -- every load of a thread in
-// flight together -- takes its moments, and applies stage 2 from the
-// registers, so the slab is read once.  The base kernel of this form takes
-// the velocities in the same order and reduces the same way.
+// Sums over a wavefront of N values at once, the totals uniform.  Two values
+// share each of the first two steps: a half-wave swap turns (a, b) into one
+// register that holds a's pair sums in the lower 32 lanes and b's in the
+// upper 32, a row swap does the same for the two 16-lane rows, and four row
+// rotations finish four values together.  21 vector instructions for four
+// values and no LDS, where a butterfly of every value takes 72 and 48 LDS
+// permutes.
 // ------------------------------------------------------------------------
-template <int D, int BS>
-__device__ __forceinline__ void fill_group_table(const Params &p, double lam, double U0, double U1, double U2,
-                                                 double *tb)
+template <bool ROW> __device__ __forceinline__ double swap_add(double a, double b)
 {
-    for (int idx = threadIdx.x; idx < p.ntab; idx += BS) {
-        const int ax = idx < p.n1d[0] ? 0 : (idx < p.n1d[0] + p.n1d[1] ? 1 : 2);
-        const double Ud = ax == 0 ? U0 : (ax == 1 ? U1 : U2);
-        const double c = p.u1d[idx] - Ud;
-        tb[idx] = exp(-lam * c * c);
-    }
-    __syncthreads();
+    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+    auto swap = [](unsigned x, unsigned y) -> uint2v {
+        if constexpr (ROW) return __builtin_bit_cast(uint2v, __builtin_amdgcn_permlane16_swap(x, y, false, false));
+        else return __builtin_bit_cast(uint2v, __builtin_amdgcn_permlane32_swap(x, y, false, false));
+    };
+    const uint2v lo = swap((unsigned)__double2loint(a), (unsigned)__double2loint(b));
+    const uint2v hi = swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b));
+    return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
 }
-
-template <int D, typename FT, bool TENSOR>
-__global__ __launch_bounds__(256) void k_push_base_r(Params p, const FT *__restrict__ fin, FT *__restrict__ acc)
+template <int CTRL> __device__ __forceinline__ double row_rotate(double x)
 {
-    constexpr int NC = Dim<D>::NC, NW = D + 2, BS = 256;
-    extern __shared__ double smem[];
-    const int i = xcd_cell(blockIdx.x);
-    if (i >= p.nc) return;
-    const int nv = p.nv, tid = threadIdx.x;
-    const CellStep<D> cs = cell_step<D>(p, i);
-    double *tb = smem;
-    double *red = smem + (TENSOR ? p.ntab : 0);
-    if constexpr (TENSOR) fill_group_table<D, BS>(p, cs.pn.lam, cs.pn.U[0], cs.pn.U[1], cs.pn.U[D - 1], tb);
-    const size_t base = (size_t)i * NC * nv;
-    double mom[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mom[m] = 0.0;
-#pragma unroll 4
-    for (int k = tid; k < nv; k += BS) {
-        double u[D], u2;
-        velocity<D>(p, k, u, u2);
-        const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-        double fp[2];
-        const double H = cs.pref_n * own_gauss<D, TENSOR>(p, tb, kx, u, cs.pn.lam, cs.pn.U);
-        shakhov<D>(u, cs.pn.U, cs.pn.lam, cs.shk_n, cs.qn, cs.bh_n, H, fp[0], fp[1]);
-        double bv[2] = {0.0, 0.0};
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double f = to_f64(fin[base + (size_t)c * nv + k]);
-            const FT sv = from_f64<FT>(fma(cs.hdt_tau, fp[c] - f, f));
-            acc[base + (size_t)c * nv + k] = sv;
-            bv[c] = to_f64(sv);
-        }
-        add_moments<D>(mom, p.w[k], u, u2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
-    }
-    block_reduce_wide<BS>(mom, red, OpAdd{});
-    if (tid == 0)
-#pragma unroll
-        for (int m = 0; m < NW; ++m) p.mom_part[(size_t)i * NW + m] = mom[m];
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true));
 }
-
-template <int D, typename FT, bool TENSOR, int NPT>
-__global__ __launch_bounds__(256) void k_push_final_r(Params p, FT *__restrict__ fout, FT *__restrict__ acc)
+__device__ __forceinline__ double read_lane(double x, int lane)
 {
-    constexpr int NC = Dim<D>::NC, NW = D + 2, NM = D * (D + 1) / 2, BS = 256;
-    // moments about U^n: m0, m1[D], m2[NM], m3[D], and for b: b0, b1[D]
-    constexpr int NMOM = 1 + D + NM + D + (NC > 1 ? 1 + D : 0);
-    extern __shared__ double smem[];
-    const int i = xcd_cell(blockIdx.x);
-    if (i >= p.nc) return;
-    const int tid = threadIdx.x, nv = p.nv;
-    const double dt = p.dt, Pr = p.Pr;
-    const size_t base = (size_t)i * NC * nv;
-    double *tb = smem;
-    double *red = smem + (TENSOR ? p.ntab : 0);
-    double Wn[NW];
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+template <int N> __device__ __forceinline__ void wave_sums(double (&v)[N])
+{
 #pragma unroll
-    for (int m = 0; m < NW; ++m) Wn[m] = p.W[(size_t)i * NW + m];
-    const Prim<D> pn = to_prim<D>(Wn);
-
-    // pass 1: the slab into registers, in its storage precision (all loads
-    // issued before any use)
-    FT v[NPT][NC];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int k = tid + BS * j;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) v[j][c] = k < nv ? acc[base + (size_t)c * nv + k] : from_f64<FT>(0.0);
-    }
-    double mm[NMOM];
-#pragma unroll
-    for (int t = 0; t < NMOM; ++t) mm[t] = 0.0;
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int k = tid + BS * j;
-        if (k < nv) {
-            const double w = p.w[k];
-            double c[D], c2 = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                c[d] = p.u[d * nv + k] - pn.U[d];
-                c2 = fma(c[d], c[d], c2);
-            }
-            const double wh = w * to_f64(v[j][0]);
-            mm[0] += wh;
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                const double whc = wh * c[a];
-                mm[1 + a] += whc;
-                mm[1 + D + NM + a] = fma(whc, c2, mm[1 + D + NM + a]);
-#pragma unroll
-                for (int bb = a; bb < D; ++bb)
-                    mm[1 + D + sym_index<D>(a, bb)] = fma(whc, c[bb], mm[1 + D + sym_index<D>(a, bb)]);
-            }
-            if constexpr (NC > 1) {
-                const double wb = w * to_f64(v[j][NC - 1]);
-                mm[1 + 2 * D + NM] += wb;
-#pragma unroll
-                for (int a = 0; a < D; ++a) mm[2 + 2 * D + NM + a] = fma(wb, c[a], mm[2 + 2 * D + NM + a]);
-            }
-        }
-    }
-    block_reduce_wide<BS>(mm, red, OpAdd{});
-    const double m0 = mm[0];
-    const double b0 = NC > 1 ? mm[1 + 2 * D + NM] : 0.0;
-    double m1[D], m3[D], b1[D], m2[NM];
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        m1[a] = mm[1 + a];
-        m3[a] = mm[1 + D + NM + a];
-        b1[a] = NC > 1 ? mm[2 + 2 * D + NM + a] : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < NM; ++t) m2[t] = mm[1 + D + t];
-
-    // macro: as in k_push_final (and macro_from_shift)
-    double mom[NW], trm2 = 0.0, um1 = 0.0, uu = 0.0;
-    mom[0] = m0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        mom[1 + a] = fma(pn.U[a], m0, m1[a]);
-        trm2 += m2[sym_index<D>(a, a)];
-        um1 = fma(pn.U[a], m1[a], um1);
-        uu = fma(pn.U[a], pn.U[a], uu);
-    }
-    mom[D + 1] = 0.5 * (trm2 + 2.0 * um1 + uu * m0 + b0);
-    double W1[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) W1[m] = Wn[m] + (mom[m] - p.mom_part[(size_t)i * NW + m]);
-    const Prim<D> p1 = to_prim<D>(W1);
-    const double tau1 = collision_time(p1.rho, p1.lam, p.mu_ref, p.omega);
-    double dl[D], d2 = 0.0, m1d = 0.0;
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        dl[a] = p1.U[a] - pn.U[a];
-        d2 = fma(dl[a], dl[a], d2);
-        m1d = fma(m1[a], dl[a], m1d);
-    }
-    double q1[D];
-    const double qden = 1.0 + Pr * dt / (2.0 * tau1);
-#pragma unroll
-    for (int a = 0; a < D; ++a) {
-        double m2d = 0.0;
-#pragma unroll
-        for (int bb = 0; bb < D; ++bb) m2d = fma(m2[sym_index<D>(a, bb)], dl[bb], m2d);
-        const double qa = m3[a] - 2.0 * m2d + d2 * m1[a] - dl[a] * trm2 + 2.0 * dl[a] * m1d - dl[a] * d2 * m0 + b1[a] -
-                          dl[a] * b0;
-        q1[a] = 0.5 * qa / qden;
-    }
-    if constexpr (TENSOR) fill_group_table<D, BS>(p, p1.lam, p1.U[0], p1.U[1], p1.U[D - 1], tb);
-
-    // pass 2: stage 2 from the registers into f, the next base into acc
-    const double pref_1 = p1.rho * pow_lam_pi<D>(p1.lam);
-    const double shk_1 = 4.0 * (1.0 - Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
-    const double a1 = 0.5 * dt / tau1, inv1 = 1.0 / (1.0 + a1);
-    const double bh_1 = Dim<D>::M / (2.0 * p1.lam);
-    double mb[NW];
-#pragma unroll
-    for (int m = 0; m < NW; ++m) mb[m] = 0.0;
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int k = tid + BS * j;
-        if (k < nv) {
-            double u[D], u2;
-            velocity<D>(p, k, u, u2);
-            const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-            double fp[2];
-            const double H = pref_1 * own_gauss<D, TENSOR>(p, tb, kx, u, p1.lam, p1.U);
-            shakhov<D>(u, p1.U, p1.lam, shk_1, q1, bh_1, H, fp[0], fp[1]);
-            double bv[2] = {0.0, 0.0};
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const FT fo = from_f64<FT>((to_f64(v[j][c]) + a1 * fp[c]) * inv1);
-                fout[base + (size_t)c * nv + k] = fo;
-                // the base from f^{n+1} as stored (bitwise what the base
-                // kernel computes from it after a restart)
-                const double fd = opaque(to_f64(fo));
-                const FT bo = from_f64<FT>(fma(a1, fp[c] - fd, fd));
-                acc[base + (size_t)c * nv + k] = bo;
-                bv[c] = to_f64(bo);
-            }
-            add_moments<D>(mb, p.w[k], u, u2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
-        }
-    }
-    block_reduce_wide<BS>(mb, red, OpAdd{});
-    if (tid == 0) {
-        bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
-#pragma unroll
-        for (int m = 0; m < NW; ++m) {
-            ok = ok && isfinite(W1[m]);
-            p.W[(size_t)i * NW + m] = W1[m];
-            const double dw = W1[m] - Wn[m];
-            p.dW2[(size_t)i * NW + m] = dw * dw;
-            p.mom_part[(size_t)i * NW + m] = mb[m];
-        }
-#pragma unroll
-        for (int d = 0; d < D; ++d) p.q[(size_t)i * D + d] = q1[d];
-        if (!ok) {
-            atomicOr(p.err, 1);
-            atomicMin(p.err + 1, i);
-        }
+    for (int g = 0; g < N; g += 4) {
+        const double b = g + 1 < N ? v[g + 1 < N ? g + 1 : 0] : 0.0, c = g + 2 < N ? v[g + 2 < N ? g + 2 : 0] : 0.0,
+                     d = g + 3 < N ? v[g + 3 < N ? g + 3 : 0] : 0.0;
+        // rows of 16 lanes: v[g], v[g + 2], v[g + 1], v[g + 3]
+        double x = swap_add<true>(swap_add<false>(v[g], b), swap_add<false>(c, d));
+        x += row_rotate<0x128>(x);
+        x += row_rotate<0x124>(x);
+        x += row_rotate<0x122>(x);
+        x += row_rotate<0x121>(x);
+        v[g] = read_lane(x, 0);
+        if (g + 1 < N) v[g + 1 < N ? g + 1 : 0] = read_lane(x, 32);
+        if (g + 2 < N) v[g + 2 < N ? g + 2 : 0] = read_lane(x, 16);
+        if (g + 3 < N) v[g + 3 < N ? g + 3 : 0] = read_lane(x, 48);
     }
 }
 
-// ------------------------------------------------------------------------
-// Push sweep with one f buffer (the in-place mode).  The velocities are taken
-// in chunks; per chunk, the base of the chunk's velocities goes into a ring of
-// one chunk per cell (its moments added to the cell's running sum), the
-// colour launches push the chunk's face fluxes into the ring, and the next
-// turn kernel writes the stage-1 values back into f -- no later launch reads
-// f^n at those velocities -- adding their moments about U^n (orders 0-3 of h,
-// 0-1 of b) to a second running sum, before it fills the ring with the next
-// chunk's base.  After the last chunk a final kernel forms
-// W^{n+1}, tau^{n+1}, q^{n+1} from the two sums and applies stage 2 in place.
-// The wall kernel runs first, while f still holds f^n at every velocity.
-// ------------------------------------------------------------------------
 template <int D> struct Shift {
     static constexpr int NC = Dim<D>::NC, NM = D * (D + 1) / 2;
     static constexpr int N = 1 + D + NM + D + (NC > 1 ? 1 + D : 0);
@@ -2840,6 +2374,394 @@ __device__ __forceinline__ void macro_from_shift(const Params &p, const double (
     }
 }
 
+// ------------------------------------------------------------------------
+// The push sweep's per-cell kernels: one workgroup per cell, thread t holding
+// the velocity pairs t, t + BS, ... of its slab in registers (NP pairs at
+// most; every velocity count a handle takes fits one of the forms of
+// launch_final).  The final kernel loads the whole stage-1 slab in one go --
+// every load of a thread in flight together -- takes its moments about U^n
+// (orders 0-3 of h, 0-1 of b), from which one wavefront forms W^{n+1},
+// tau^{n+1} and the heat flux about U^{n+1} (macro_from_shift), and applies
+// stage 2 from the registers into f and the next step's base into acc, so
+// that the slab is read once.  The base kernel takes the velocities in the
+// same order and reduces the same way, so both give the same bits.  Bound by
+// the latency of a cell's phases at two workgroups a CU (VALUs half busy);
+// 107,118 cells x 4,548: 3.78 -> 2.90 ms in FP64 (11.7 GB, 4.0 TB/s), 3.27 ->
+// 3.00 in FP32; 50,688 x 13,824 in FP64 7.36 -> 4.95 ms; against one wavefront
+// per cell (and FP64 slabs of at most 24 values in 256 threads), butterfly
+// sums and the points read from memory in both passes.
+// ------------------------------------------------------------------------
+// Values k0, k0 + 1 (k0 < nv, even) of an array: one access where nv is even
+// (every slab then starts at an even element), else two.
+template <typename T> __device__ __forceinline__ void load_pair(const T *__restrict__ q, int k0, int nv, double &a, double &b)
+{
+    if (nv & 1) {
+        a = to_f64(q[k0]);
+        b = k0 + 1 < nv ? to_f64(q[k0 + 1]) : 0.0;
+    } else {
+        load2<T>(q + k0, a, b);
+    }
+}
+template <typename T> __device__ __forceinline__ void store_pair(T *__restrict__ q, int k0, int nv, T a, T b)
+{
+    if (nv & 1) {
+        q[k0] = a;
+        if (k0 + 1 < nv) q[k0 + 1] = b;
+    } else {
+        store2<T>(q + k0, a, b);
+    }
+}
+// A velocity pair's weights (zero past the last velocity) and, where the set
+// is tabulated, its table positions, else its points.  The streaming kernels
+// take the points of a tabulated set from LDS: the 24 bytes a velocity that a
+// point takes, twice a cell, were two thirds of what these kernels drew from
+// L2, which they ran at the rate of (12 TB/s).
+template <int D, bool TENSOR> struct VelPair {
+    double w[2], u[TENSOR ? 1 : 2][D];
+    unsigned kx[2];
+    __device__ __forceinline__ void load(const Params &p, int k0)
+    {
+        load_pair<double>(p.w, k0, p.nv, w[0], w[1]);
+        kx[0] = kx[1] = 0u;
+        if constexpr (TENSOR) {
+            if (p.nv & 1) {
+                kx[0] = (unsigned)p.kidx[k0];
+                if (k0 + 1 < p.nv) kx[1] = (unsigned)p.kidx[k0 + 1];
+            } else {
+                const int2 x = *reinterpret_cast<const int2 *>(p.kidx + k0);
+                kx[0] = (unsigned)x.x;
+                kx[1] = (unsigned)x.y;
+            }
+        } else {
+#pragma unroll
+            for (int d = 0; d < D; ++d) load_pair<double>(p.u + (size_t)d * p.nv, k0, p.nv, u[0][d], u[1][d]);
+        }
+    }
+    // peculiar velocity of element e: from the table of u_d - U_d, or the points
+    __device__ __forceinline__ void peculiar_of(int e, const double *tc, const double (&U)[D], double (&c)[D],
+                                                double &c2) const
+    {
+        if constexpr (TENSOR) {
+            c2 = 0.0;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                c[d] = tc[kx[e] >> (10 * d) & 1023u];
+                c2 = fma(c[d], c[d], c2);
+            }
+        } else {
+            peculiar<D>(u[e], U, c, c2);
+        }
+    }
+    // the same and the Gaussian, from the table of (u_d - U_d, exp(-lam (u_d - U_d)^2))
+    __device__ __forceinline__ double gauss_of(int e, const double2 *tg, const double (&U)[D], double lam,
+                                               double (&c)[D], double &c2) const
+    {
+        if constexpr (TENSOR) {
+            double g = 1.0;
+            c2 = 0.0;
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const double2 x = tg[kx[e] >> (10 * d) & 1023u];
+                c[d] = x.x;
+                c2 = fma(c[d], c[d], c2);
+                g = d == 0 ? x.y : g * x.y;
+            }
+            return g;
+        } else {
+            peculiar<D>(u[e], U, c, c2);
+            return exp(-lam * c2);
+        }
+    }
+};
+
+__device__ __forceinline__ double axis_point(const Params &p, int idx, double U0, double U1, double U2)
+{
+    return p.u1d[idx] - (idx < p.n1d[0] ? U0 : (idx < p.n1d[0] + p.n1d[1] ? U1 : U2));
+}
+template <int BS>
+__device__ __forceinline__ void fill_points(const Params &p, double U0, double U1, double U2, double *tc)
+{
+    for (int idx = threadIdx.x; idx < p.ntab; idx += BS) tc[idx] = axis_point(p, idx, U0, U1, U2);
+}
+template <int BS>
+__device__ __forceinline__ void fill_gauss(const Params &p, double lam, double U0, double U1, double U2, double2 *tg)
+{
+    for (int idx = threadIdx.x; idx < p.ntab; idx += BS) {
+        const double c = axis_point(p, idx, U0, U1, U2);
+        tg[idx] = make_double2(c, exp(-lam * c * c));
+    }
+}
+
+template <int D, int BS>
+__device__ __forceinline__ void fill_group_table(const Params &p, double lam, double U0, double U1, double U2,
+                                                 double *tb)
+{
+    for (int idx = threadIdx.x; idx < p.ntab; idx += BS) {
+        const int ax = idx < p.n1d[0] ? 0 : (idx < p.n1d[0] + p.n1d[1] ? 1 : 2);
+        const double Ud = ax == 0 ? U0 : (ax == 1 ? U1 : U2);
+        const double c = p.u1d[idx] - Ud;
+        tb[idx] = exp(-lam * c * c);
+    }
+    __syncthreads();
+}
+
+// conservative moments (1, u, (|u|^2 h + b) / 2) from those of c = u - U
+template <int D> __device__ __forceinline__ double recentred(const double *m, const double (&U)[D], int n)
+{
+    if (n == 0) return m[0];
+    double um = 0.0, uu = 0.0, r = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        um = fma(U[d], m[1 + d], um);
+        uu = fma(U[d], U[d], uu);
+        if (n == 1 + d) r = fma(U[d], m[0], m[1 + d]);
+    }
+    return n == D + 1 ? fma(0.5 * uu, m[0], um) + m[D + 1] : r;
+}
+
+// moments of the workgroup's wavefronts summed in their order by threads 0..N
+template <int BS, int N> __device__ __forceinline__ double group_total(const double *red, int n)
+{
+    double s = red[n];
+    for (int w = 1; w < BS / 64; ++w) s += red[w * N + n];
+    return s;
+}
+
+// the base's moments, from the wavefronts' sums about U (first wavefront)
+template <int D, int BS>
+__device__ __forceinline__ void store_base_moments(const Params &p, int i, const double *red, const double (&U)[D])
+{
+    constexpr int NW = D + 2;
+    if (threadIdx.x >= 64) return;
+    const int n = threadIdx.x;
+    const double s = n < NW ? group_total<BS, NW>(red, n) : 0.0;
+    double m[NW];
+#pragma unroll
+    for (int t = 0; t < NW; ++t) m[t] = read_lane(s, t);
+    const double r = recentred<D>(m, U, n);
+    if (n < NW) p.mom_part[(size_t)i * NW + n] = r;
+}
+
+template <int D, typename FT, bool TENSOR, int BS>
+__global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict__ fin,
+                                                  typename AccOf<FT>::T *__restrict__ acc)
+{
+    using AT = typename AccOf<FT>::T;
+    constexpr int NC = Dim<D>::NC, NW = D + 2;
+    extern __shared__ double smem[];
+    const int i = xcd_cell(blockIdx.x);
+    if (i >= p.nc) return;
+    const int nv = p.nv, tid = threadIdx.x;
+    const CellStep<D> cs = cell_step<D>(p, i);
+    double2 *tg = reinterpret_cast<double2 *>(smem);
+    double *red = smem + (TENSOR ? 2 * p.ntab : 0);
+    if constexpr (TENSOR) {
+        fill_gauss<BS>(p, cs.pn.lam, cs.pn.U[0], cs.pn.U[1], cs.pn.U[D - 1], tg);
+        __syncthreads();
+    }
+    const size_t base = (size_t)i * NC * nv;
+    double mom[NW];
+#pragma unroll
+    for (int m = 0; m < NW; ++m) mom[m] = 0.0;
+#pragma unroll 2
+    for (int k0 = 2 * tid; k0 < nv; k0 += 2 * BS) {
+        double f[NC][2];
+        VelPair<D, TENSOR> vp;
+        vp.load(p, k0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) load_pair<FT>(fin + base + (size_t)c * nv, k0, nv, f[c][0], f[c][1]);
+        AT sv[NC][2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            double c3[D], c2, fp[2], bv[2] = {0.0, 0.0};
+            const double H = cs.pref_n * vp.gauss_of(e, tg, cs.pn.U, cs.pn.lam, c3, c2);
+            shakhov_at<D>(c3, c2, cs.pn.lam, cs.shk_n, cs.qn, cs.bh_n, H, fp[0], fp[1]);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                sv[c][e] = from_f64<AT>(fma(cs.hdt_tau, fp[c] - f[c][e], f[c][e]));
+                bv[c] = to_f64(sv[c][e]);
+            }
+            add_moments<D>(mom, vp.w[e], c3, c2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, sv[c][0], sv[c][1]);
+    }
+    wave_sums<NW>(mom);
+    if ((tid & 63) == 0)
+#pragma unroll
+        for (int m = 0; m < NW; ++m) red[(tid >> 6) * NW + m] = mom[m];
+    __syncthreads();
+    store_base_moments<D, BS>(p, i, red, cs.pn.U);
+}
+
+template <int D, typename FT, bool TENSOR, int BS, int NP>
+__global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fout, typename AccOf<FT>::T *__restrict__ acc)
+{
+    using AT = typename AccOf<FT>::T;
+    constexpr int NC = Dim<D>::NC, NW = D + 2, N = Shift<D>::N;
+    extern __shared__ double smem[];
+    const int i = xcd_cell(blockIdx.x);
+    if (i >= p.nc) return;
+    const int tid = threadIdx.x, nv = p.nv;
+    const size_t base = (size_t)i * NC * nv;
+    double2 *tg = reinterpret_cast<double2 *>(smem);  // about U^{n+1}
+    double *tc = smem + (TENSOR ? 2 * p.ntab : 0);    // about U^n
+    double *red = tc + (TENSOR ? p.ntab : 0), *res = red + (BS / 64) * N;
+    double Wn[NW];
+#pragma unroll
+    for (int m = 0; m < NW; ++m) Wn[m] = p.W[(size_t)i * NW + m];
+    const Prim<D> pn = to_prim<D>(Wn);
+
+    // pass 1: the slab into registers, in its storage precision (all loads
+    // issued before any use), its moments about U^n
+    AT v[NP][NC][2];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int k0 = 2 * (tid + BS * j);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            v[j][c][0] = v[j][c][1] = from_f64<AT>(0.0);
+            if (k0 < nv) {
+                const AT *q = acc + base + (size_t)c * nv + k0;
+                if (nv & 1) {
+                    v[j][c][0] = q[0];
+                    if (k0 + 1 < nv) v[j][c][1] = q[1];
+                } else {
+                    const typename Vec2<AT>::T x = *reinterpret_cast<const typename Vec2<AT>::T *>(q);
+                    v[j][c][0] = x.x;
+                    v[j][c][1] = x.y;
+                }
+            }
+        }
+    }
+    if constexpr (TENSOR) {
+        fill_points<BS>(p, pn.U[0], pn.U[1], pn.U[D - 1], tc);
+        __syncthreads();
+    }
+    double mm[N];
+#pragma unroll
+    for (int t = 0; t < N; ++t) mm[t] = 0.0;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int k0 = 2 * (tid + BS * j);
+        if (k0 < nv) {
+            VelPair<D, TENSOR> vp;
+            vp.load(p, k0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                double c[D], c2;
+                vp.peculiar_of(e, tc, pn.U, c, c2);
+                add_shift_moments<D>(mm, vp.w[e], c, c2, to_f64(v[j][0][e]), NC > 1 ? to_f64(v[j][NC - 1][e]) : 0.0);
+            }
+        }
+    }
+    wave_sums<N>(mm);
+    if ((tid & 63) == 0)
+#pragma unroll
+        for (int t = 0; t < N; ++t) red[(tid >> 6) * N + t] = mm[t];
+    __syncthreads();
+    // macro, by the first wavefront for the others
+    if (tid < 64) {
+        const double s = tid < N ? group_total<BS, N>(red, tid) : 0.0;
+#pragma unroll
+        for (int t = 0; t < N; ++t) mm[t] = read_lane(s, t);
+        double W1[NW], tau1, q1[D];
+        Prim<D> p1;
+        macro_from_shift<D>(p, mm, Wn, pn, p.mom_part + (size_t)i * NW, W1, p1, tau1, q1);
+        if (tid == 0) {
+            res[0] = p1.lam;
+            res[1] = p1.rho * pow_lam_pi<D>(p1.lam);
+            res[2] = 4.0 * (1.0 - p.Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
+            res[3] = 0.5 * p.dt / tau1;
+            bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                res[4 + d] = p1.U[d];
+                res[4 + D + d] = q1[d];
+                p.q[(size_t)i * D + d] = q1[d];
+            }
+#pragma unroll
+            for (int m = 0; m < NW; ++m) {
+                ok = ok && isfinite(W1[m]);
+                p.W[(size_t)i * NW + m] = W1[m];
+                const double dw = W1[m] - Wn[m];
+                p.dW2[(size_t)i * NW + m] = dw * dw;
+            }
+            if (!ok) {
+                atomicOr(p.err, 1);
+                atomicMin(p.err + 1, i);
+            }
+        }
+    }
+    __syncthreads();
+    const double lam = res[0], pref = res[1], shk = res[2], a1 = res[3], inv1 = 1.0 / (1.0 + a1);
+    const double bh = Dim<D>::M / (2.0 * lam);
+    double U[D], q1[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        U[d] = res[4 + d];
+        q1[d] = res[4 + D + d];
+    }
+    if constexpr (TENSOR) {
+        fill_gauss<BS>(p, lam, U[0], U[1], U[D - 1], tg);
+        __syncthreads();
+    }
+
+    // pass 2: stage 2 from the registers into f, the next base into acc
+    double mb[NW];
+#pragma unroll
+    for (int m = 0; m < NW; ++m) mb[m] = 0.0;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+        const int k0 = 2 * (tid + BS * j);
+        if (k0 < nv) {
+            VelPair<D, TENSOR> vp;
+            vp.load(p, k0);
+            FT fo[NC][2];
+            AT bo[NC][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                double c3[D], c2, fp[2], bv[2] = {0.0, 0.0};
+                const double H = pref * vp.gauss_of(e, tg, U, lam, c3, c2);
+                shakhov_at<D>(c3, c2, lam, shk, q1, bh, H, fp[0], fp[1]);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    fo[c][e] = from_f64<FT>((to_f64(v[j][c][e]) + a1 * fp[c]) * inv1);
+                    // the base from f^{n+1} as stored (bitwise what the base
+                    // kernel computes from it after a restart)
+                    const double fd = opaque(to_f64(fo[c][e]));
+                    bo[c][e] = from_f64<AT>(fma(a1, fp[c] - fd, fd));
+                    bv[c] = to_f64(bo[c][e]);
+                }
+                add_moments<D>(mb, vp.w[e], c3, c2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                store_pair<FT>(fout + base + (size_t)c * nv, k0, nv, fo[c][0], fo[c][1]);
+                store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, bo[c][0], bo[c][1]);
+            }
+        }
+    }
+    wave_sums<NW>(mb);
+    if ((tid & 63) == 0)
+#pragma unroll
+        for (int m = 0; m < NW; ++m) red[(tid >> 6) * NW + m] = mb[m];
+    __syncthreads();
+    store_base_moments<D, BS>(p, i, red, U);
+}
+
+// ------------------------------------------------------------------------
+// Push sweep with one f buffer (the in-place mode).  The velocities are taken
+// in chunks; per chunk, the base of the chunk's velocities goes into a ring of
+// one chunk per cell (its moments added to the cell's running sum), the
+// colour launches push the chunk's face fluxes into the ring, and the next
+// turn kernel writes the stage-1 values back into f -- no later launch reads
+// f^n at those velocities -- adding their moments about U^n (orders 0-3 of h,
+// 0-1 of b) to a second running sum, before it fills the ring with the next
+// chunk's base.  After the last chunk a final kernel forms
+// W^{n+1}, tau^{n+1}, q^{n+1} from the two sums and applies stage 2 in place.
+// The wall kernel runs first, while f still holds f^n at every velocity.
+// ------------------------------------------------------------------------
 // The turn between two chunks, per cell: the previous chunk's stage-1
 // values from the ring back into f, their moments about U^n added to mom_s;
 // then the base of the next chunk's velocities into the ring, its moments
@@ -2988,45 +2910,51 @@ __global__ __launch_bounds__(256) void k_push_final_inplace(Params p, FT *__rest
 // push sweep launches: the stage-1 base (when stale), the wall cells, one
 // launch per colour (split over velocities when small), the final kernel
 // ------------------------------------------------------------------------
+// The form of the per-cell kernels for a velocity count: workgroup size and
+// pairs per thread.  Larger slabs take more threads rather than more pairs a
+// thread: at 4,548 velocities 5 pairs in 512 threads 3.27 ms, 10 in 256 3.32,
+// 20 in 128 3.72 (107,118 cells, FP64, before the points came from LDS), and
+// held to more waves a SIMD than its 117 registers allow it spills (4.8-6.7).
+template <int D, typename FT, bool TENSOR, int BS>
+void launch_base_form(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
+{
+    const size_t lds = sizeof(double) * ((TENSOR ? 2 * (size_t)p.ntab : 0) + (BS / 64) * (D + 2));
+    hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, BS>), dim3(sweep_grid(p.nc)), dim3(BS), lds, s, p, f, acc);
+}
+template <int D, typename FT, bool TENSOR>
+void launch_base(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
+{
+    if (p.nv <= 1536) launch_base_form<D, FT, TENSOR, 256>(p, f, acc, s);
+    else if (p.nv <= 5120) launch_base_form<D, FT, TENSOR, 512>(p, f, acc, s);
+    else launch_base_form<D, FT, TENSOR, 1024>(p, f, acc, s);
+}
+template <int D, typename FT, bool TENSOR, int BS, int NP>
+void launch_final_form(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
+{
+    const size_t lds = sizeof(double) * ((TENSOR ? 3 * (size_t)p.ntab : 0) + (BS / 64) * Shift<D>::N + 4 + 2 * D);
+    hipLaunchKernelGGL((k_push_final<D, FT, TENSOR, BS, NP>), dim3(sweep_grid(p.nc)), dim3(BS), lds, s, p, f, acc);
+}
+template <int D, typename FT, bool TENSOR>
+void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
+{
+    if (p.nv <= 1536) launch_final_form<D, FT, TENSOR, 256, 3>(p, f, acc, s);
+    else if (p.nv <= 3072) launch_final_form<D, FT, TENSOR, 512, 3>(p, f, acc, s);
+    else if (p.nv <= 5120) launch_final_form<D, FT, TENSOR, 512, 5>(p, f, acc, s);
+    else launch_final_form<D, FT, TENSOR, 1024, 8>(p, f, acc, s);  // up to 16,384 velocities
+}
+
 template <int D, typename FT, bool TENSOR>
 hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int *cells, const int *coff, int ncol,
                   const int *wall_cells, int n_wall_cells, hipStream_t s)
 {
-    constexpr int MF = Dim<D>::MF, NW = D + 2, NC = Dim<D>::NC, BS = 256;
+    constexpr int MF = Dim<D>::MF, NW = D + 2, BS = 256;
     using AT = typename AccOf<FT>::T;
     const FT *fin = static_cast<const FT *>(fv);
     FT *f = static_cast<FT *>(fv);
     AT *acc = static_cast<AT *>(av);
     const size_t tab = sizeof(double) * (size_t)(MF + 1) * (TENSOR ? p.ntab : 0);
     const size_t red = sizeof(double) * ((BS / 64) * (2 * NW + 2) + MF);
-    const unsigned gc = (unsigned)sweep_grid(p.nc);
-    // the per-cell streaming kernels: a wavefront per cell, four per group;
-    // velocity pairs when the count is even (every slab offset is then
-    // even: aligned 2-wide accesses)
-    const unsigned gw = (unsigned)sweep_grid((p.nc + kPushCellsPerGroup - 1) / kPushCellsPerGroup);
-    const size_t ltab = sizeof(double) * (size_t)kPushCellsPerGroup * (TENSOR ? p.ntab : 0);
-    const bool v2 = p.nv % 2 == 0;
-    // the register-resident form for FP64 f where a thread's share of the
-    // slab fits in 48 registers (n_comp x NPT values; with FP32 f it measured
-    // slower than the wavefront form)
-    const int npt = (p.nv + 255) / 256;
-    const int slab_regs = NC * 2;
-    int reg_form = 0;
-    if (sizeof(FT) == 8) {
-        if (npt <= 12 && 12 * slab_regs <= 48) reg_form = 12;
-        else if (npt <= 18 && 18 * slab_regs <= 48) reg_form = 18;
-        else if (npt <= 24 && 24 * slab_regs <= 48) reg_form = 24;
-    }
-    const size_t lreg = sizeof(double) * ((TENSOR ? (size_t)p.ntab : 0) + 5 * 16);
-    if (need_base && reg_form) {
-        if constexpr (sizeof(FT) == 8)
-            hipLaunchKernelGGL((k_push_base_r<D, FT, TENSOR>), dim3(gc), dim3(256), lreg, s, p, fin, acc);
-    } else if (need_base) {
-        if (v2)
-            hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, true>), dim3(gw), dim3(256), ltab, s, p, fin, acc);
-        else
-            hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, false>), dim3(gw), dim3(256), ltab, s, p, fin, acc);
-    }
+    if (need_base) launch_base<D, FT, TENSOR>(p, fin, acc, s);
     if (n_wall_cells > 0)
         hipLaunchKernelGGL((k_push_wall<D, FT, BS, TENSOR>), dim3(n_wall_cells), dim3(BS), tab + red, s, p, fin,
                            wall_cells, n_wall_cells);
@@ -3043,19 +2971,7 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
             hipLaunchKernelGGL((k_push<D, FT, BS, false>), grid, dim3(BS), tab + red, s, p, fin, acc, cells + coff[c],
                                n, 0, p.nv, p.nv, ks);
     }
-    if (reg_form) {
-        if constexpr (sizeof(FT) == 8) {
-            if (reg_form == 12)
-                hipLaunchKernelGGL((k_push_final_r<D, FT, TENSOR, 12>), dim3(gc), dim3(256), lreg, s, p, f, acc);
-            else if (reg_form == 18)
-                hipLaunchKernelGGL((k_push_final_r<D, FT, TENSOR, 18>), dim3(gc), dim3(256), lreg, s, p, f, acc);
-            else
-                hipLaunchKernelGGL((k_push_final_r<D, FT, TENSOR, 24>), dim3(gc), dim3(256), lreg, s, p, f, acc);
-        }
-    } else if (v2)
-        hipLaunchKernelGGL((k_push_final<D, FT, TENSOR, true>), dim3(gw), dim3(256), ltab, s, p, f, acc);
-    else
-        hipLaunchKernelGGL((k_push_final<D, FT, TENSOR, false>), dim3(gw), dim3(256), ltab, s, p, f, acc);
+    launch_final<D, FT, TENSOR>(p, f, acc, s);
     return hipGetLastError();
 }
 
