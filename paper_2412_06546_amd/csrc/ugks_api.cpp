@@ -36,6 +36,7 @@ struct ugks {
     double *mom_part = nullptr;    // moments of the chunks swept so far (in place) or of the stage-1 base (push)
     double *rho_w = nullptr;       // wall densities (in place, push)
     double *mom_s = nullptr;       // push sweep in place: stage-1 moments about U^n summed over the chunks
+    void *cconst = nullptr;        // push sweep in place: the cells' constants of the step
     // push sweep: colour lists (device cells, host offsets), wall cells,
     // face -> wall ordinal; whether the second buffer holds the stage-1 base
     // of the current f, and whether the last step was a push step (the wall
@@ -555,8 +556,9 @@ size_t plan_bytes(int D, size_t nc, size_t nf, size_t nv, int nbc, int fstore, s
     }
     if (push) {  // colour lists, wall cells, face -> wall ordinal
         b += nbytes<int>(nc) + nbytes<int>(nwallf) + nbytes<int>(nf);
-        if (mem_mode == UGKS_MEM_IN_PLACE)  // the running moments about U^n
-            b += nbytes<double>(nc * (size_t)shift_moments(D));
+        if (mem_mode == UGKS_MEM_IN_PLACE)  // the running moments about U^n, the cells' constants
+            b += nbytes<double>(nc * (size_t)shift_moments(D)) +
+                 (D == 2 ? nbytes<CellConst<2>>(nc) : nbytes<CellConst<3>>(nc));
         else  // base moments, wall densities
             b += nbytes<double>(nc * NW) + nbytes<double>(nc * (D == 2 ? Dim<2>::MF : Dim<3>::MF));
     }
@@ -610,7 +612,7 @@ void release(ugks_t *h)
     if (h->done_ev) (void)hipEventDestroy(h->done_ev);
     void *ptrs[] = {h->f[0], h->f[1], h->cgeo, h->fgeo, h->feq, h->u, h->w, h->bcp, h->W, h->q, h->gW, h->dW2,
                     h->cell_dt, h->res, h->err, h->u1d, h->kidx, h->wallf, h->wallF, h->surf, h->ring, h->mom_part, h->rho_w,
-                    h->mom_s, h->colour_cells, h->wall_cells, h->wall_index};
+                    h->mom_s, h->cconst, h->colour_cells, h->wall_cells, h->wall_index};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -763,7 +765,10 @@ extern "C" int ugks_create(const ugks_mesh_t *mesh, const ugks_vgrid_t *vgrid, c
             h->rho_w = dev_alloc<double>(h, nc * (size_t)(D == 2 ? Dim<2>::MF : Dim<3>::MF));
             hip_check(hipMemsetAsync(h->rho_w, 0, sizeof(double) * nc * (D == 2 ? Dim<2>::MF : Dim<3>::MF),
                                      h->stream), "hipMemsetAsync");
-            if (h->push) h->mom_s = dev_alloc<double>(h, nc * (size_t)shift_moments(D));
+            if (h->push) {
+                h->mom_s = dev_alloc<double>(h, nc * (size_t)shift_moments(D));
+                h->cconst = D == 2 ? (void *)dev_alloc<CellConst<2>>(h, nc) : (void *)dev_alloc<CellConst<3>>(h, nc);
+            }
         }
         upload(h->u, uT.data(), sizeof(double) * uT.size(), h->stream);
         upload(h->w, wP.data(), sizeof(double) * nv, h->stream);
@@ -808,6 +813,7 @@ extern "C" int ugks_create(const ugks_mesh_t *mesh, const ugks_vgrid_t *vgrid, c
         P.wall_index = h->wall_index;
         P.wflux = h->wallF;
         P.mom_s = h->mom_s;
+        P.cconst = h->cconst;
 
         // time step (Algorithm 1's first step), fixed for the run
         hip_check(launch_cfl(P, h->cell_dt, h->stream), "k_cfl launch");

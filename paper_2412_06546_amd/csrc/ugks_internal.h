@@ -67,6 +67,13 @@ template <int D> struct alignas(16) FaceEq {
     double bh, d0, d1[D];              // 2D only (b); zero in 3D
 };
 
+// A cell's constants at t^n for the streaming kernels of the push sweep in
+// place, which visit every cell once per velocity chunk: written once a step
+// by the prologue.
+template <int D> struct alignas(16) CellConst {
+    double U[D], lam, pref, shk, q[D], hdt_tau, bh;
+};
+
 struct Params {
     int dim, fstore;
     int nc, nf, nv;
@@ -104,6 +111,7 @@ struct Params {
     // push sweep with one f buffer: the stage-1 moments about U^n summed over
     // the chunks so far [cell][Shift<D>::N]
     double *mom_s;
+    void *cconst;  // CellConst per cell (push sweep in place), else NULL
 };
 
 // One case of a batched launch (several cases advanced by the same kernels):

@@ -114,33 +114,6 @@ __device__ __forceinline__ void block_reduce(double (&v)[N], double *lds, Op op)
     __syncthreads();
 }
 
-// The same reduction for wide workgroups (many wavefronts): one thread per
-// value sums the wavefronts' results, in the same fixed order, and the
-// totals are broadcast through LDS; lds holds (BS / 64 + 1) * N doubles.
-template <int BS, int N, typename Op>
-__device__ __forceinline__ void block_reduce_wide(double (&v)[N], double *lds, Op op)
-{
-    constexpr int NWAVE = BS / 64;
-#pragma unroll
-    for (int n = 0; n < N; ++n)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[n] = op(v[n], __shfl_xor(v[n], off, 64));
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int n = 0; n < N; ++n) lds[wid * N + n] = v[n];
-    __syncthreads();
-    if ((int)threadIdx.x < N) {
-        double s = lds[threadIdx.x];
-        for (int w = 1; w < NWAVE; ++w) s = op(s, lds[w * N + threadIdx.x]);
-        lds[NWAVE * N + threadIdx.x] = s;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int n = 0; n < N; ++n) v[n] = lds[NWAVE * N + n];
-    __syncthreads();
-}
-
 struct OpAdd {
     __device__ double operator()(double a, double b) const { return a + b; }
 };
@@ -550,11 +523,30 @@ __global__ __launch_bounds__(256) void k_moments(Params p, const FT *__restrict_
 // ------------------------------------------------------------------------
 // Algorithm 1, macroscopic reconstruction: limited gradients of the conservative variables
 // ------------------------------------------------------------------------
+// The constants of f+^n and of the source in cell i.
+template <int D> __device__ __forceinline__ CellConst<D> cell_const(const Params &p, int i)
+{
+    const Prim<D> pn = to_prim<D>(p.W + (size_t)i * (D + 2));
+    CellConst<D> c;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        c.U[d] = pn.U[d];
+        c.q[d] = p.q[(size_t)i * D + d];
+    }
+    c.lam = pn.lam;
+    c.pref = pn.rho * pow_lam_pi<D>(pn.lam);
+    c.shk = 4.0 * (1.0 - p.Pr) * pn.lam * pn.lam / (5.0 * pn.rho);
+    c.hdt_tau = 0.5 * p.dt / collision_time(pn.rho, pn.lam, p.mu_ref, p.omega);
+    c.bh = Dim<D>::M / (2.0 * pn.lam);
+    return c;
+}
+
 template <int D>
 __device__ __forceinline__ void cell_grad(const Params p, int i)
 {
     constexpr int NW = D + 2, MF = Dim<D>::MF;
     if (i >= p.nc) return;
+    if (p.cconst) static_cast<CellConst<D> *>(p.cconst)[i] = cell_const<D>(p, i);
     const CellGeo<D> &g = static_cast<const CellGeo<D> *>(p.cgeo)[i];
     const int nf = g.nf;
     // the cell's W and its neighbours' (the cell's own where a slot has no
@@ -1603,43 +1595,6 @@ template <> struct AccOf<bf16s> {
     using T = float;
 };
 
-// velocity k's components of the velocity set
-template <int D>
-__device__ __forceinline__ void velocity(const Params &p, int k, double (&u)[D], double &u2)
-{
-    u2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        u[d] = p.u[d * p.nv + k];
-        u2 = fma(u[d], u[d], u2);
-    }
-}
-
-// A lookup in a cell's own table of Gaussian factors.
-template <int D>
-__device__ __forceinline__ double wave_table_gauss(const Params &p, const double *tb, unsigned kx)
-{
-    double g = tb[kx & 1023u] * tb[kx >> 10 & 1023u];
-    if constexpr (D == 3) g *= tb[kx >> 20];
-    return g;
-}
-template <int D, bool TENSOR>
-__device__ __forceinline__ double own_gauss(const Params &p, const double *tb, unsigned kx, const double (&u)[D],
-                                            double lam, const double (&U)[D])
-{
-    if constexpr (TENSOR) {
-        return wave_table_gauss<D>(p, tb, kx);
-    } else {
-        double c2 = 0.0;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const double c = u[d] - U[d];
-            c2 += c * c;
-        }
-        return exp(-lam * c2);
-    }
-}
-
 // Wall faces of cell i (Section 2.5): per wall face, the incident particles'
 // mass flux (free transport of the interior reconstruction) and the
 // unit-density reflected one, summed over velocities, give rho_w
@@ -1884,7 +1839,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(D == 3 ? 6 :
 // with at least four iterations a share, a colour launch of a 2,197-cell
 // channel (1,331 velocities) took 24.2 us and now takes 13.0, one of a
 // 4,096-cell box with 2,145 scattered velocities 32.8 and now 23.3.
-constexpr int kPushFill = 8192;
+constexpr int kPushFill = 4096;
 inline int push_ksplit(int n, int kn, int bs)
 {
     const int iters = (kn + bs - 1) / bs;  // velocity iterations of one workgroup
@@ -2391,26 +2346,30 @@ __device__ __forceinline__ void macro_from_shift(const Params &p, const double (
 // per cell (and FP64 slabs of at most 24 values in 256 threads), butterfly
 // sums and the points read from memory in both passes.
 // ------------------------------------------------------------------------
-// Values k0, k0 + 1 (k0 < nv, even) of an array: one access where nv is even
-// (every slab then starts at an even element), else two.
-template <typename T> __device__ __forceinline__ void load_pair(const T *__restrict__ q, int k0, int nv, double &a, double &b)
+// Elements k, k + 1 of an array of n (k < n): one access where the pair is
+// aligned (pairs from even elements of slabs that start at even elements),
+// else two; zero past the end.
+template <typename T>
+__device__ __forceinline__ void load_pair(const T *__restrict__ q, int k, int n, bool aligned, double &a, double &b)
 {
-    if (nv & 1) {
-        a = to_f64(q[k0]);
-        b = k0 + 1 < nv ? to_f64(q[k0 + 1]) : 0.0;
+    if (aligned) {
+        load2<T>(q + k, a, b);
     } else {
-        load2<T>(q + k0, a, b);
+        a = to_f64(q[k]);
+        b = k + 1 < n ? to_f64(q[k + 1]) : 0.0;
     }
 }
-template <typename T> __device__ __forceinline__ void store_pair(T *__restrict__ q, int k0, int nv, T a, T b)
+template <typename T>
+__device__ __forceinline__ void store_pair(T *__restrict__ q, int k, int n, bool aligned, T a, T b)
 {
-    if (nv & 1) {
-        q[k0] = a;
-        if (k0 + 1 < nv) q[k0 + 1] = b;
+    if (aligned) {
+        store2<T>(q + k, a, b);
     } else {
-        store2<T>(q + k0, a, b);
+        q[k] = a;
+        if (k + 1 < n) q[k + 1] = b;
     }
 }
+
 // A velocity pair's weights (zero past the last velocity) and, where the set
 // is tabulated, its table positions, else its points.  The streaming kernels
 // take the points of a tabulated set from LDS: the 24 bytes a velocity that a
@@ -2419,14 +2378,15 @@ template <typename T> __device__ __forceinline__ void store_pair(T *__restrict__
 template <int D, bool TENSOR> struct VelPair {
     double w[2], u[TENSOR ? 1 : 2][D];
     unsigned kx[2];
-    __device__ __forceinline__ void load(const Params &p, int k0)
+    // velocities k0, k0 + 1 of those below n
+    __device__ __forceinline__ void load(const Params &p, int k0, int n, bool aligned)
     {
-        load_pair<double>(p.w, k0, p.nv, w[0], w[1]);
+        load_pair<double>(p.w, k0, n, aligned, w[0], w[1]);
         kx[0] = kx[1] = 0u;
         if constexpr (TENSOR) {
-            if (p.nv & 1) {
+            if (!aligned) {
                 kx[0] = (unsigned)p.kidx[k0];
-                if (k0 + 1 < p.nv) kx[1] = (unsigned)p.kidx[k0 + 1];
+                if (k0 + 1 < n) kx[1] = (unsigned)p.kidx[k0 + 1];
             } else {
                 const int2 x = *reinterpret_cast<const int2 *>(p.kidx + k0);
                 kx[0] = (unsigned)x.x;
@@ -2434,7 +2394,7 @@ template <int D, bool TENSOR> struct VelPair {
             }
         } else {
 #pragma unroll
-            for (int d = 0; d < D; ++d) load_pair<double>(p.u + (size_t)d * p.nv, k0, p.nv, u[0][d], u[1][d]);
+            for (int d = 0; d < D; ++d) load_pair<double>(p.u + (size_t)d * p.nv, k0, n, aligned, u[0][d], u[1][d]);
         }
     }
     // peculiar velocity of element e: from the table of u_d - U_d, or the points
@@ -2492,19 +2452,6 @@ __device__ __forceinline__ void fill_gauss(const Params &p, double lam, double U
     }
 }
 
-template <int D, int BS>
-__device__ __forceinline__ void fill_group_table(const Params &p, double lam, double U0, double U1, double U2,
-                                                 double *tb)
-{
-    for (int idx = threadIdx.x; idx < p.ntab; idx += BS) {
-        const int ax = idx < p.n1d[0] ? 0 : (idx < p.n1d[0] + p.n1d[1] ? 1 : 2);
-        const double Ud = ax == 0 ? U0 : (ax == 1 ? U1 : U2);
-        const double c = p.u1d[idx] - Ud;
-        tb[idx] = exp(-lam * c * c);
-    }
-    __syncthreads();
-}
-
 // conservative moments (1, u, (|u|^2 h + b) / 2) from those of c = u - U
 template <int D> __device__ __forceinline__ double recentred(const double *m, const double (&U)[D], int n)
 {
@@ -2552,6 +2499,7 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
     const int i = xcd_cell(blockIdx.x);
     if (i >= p.nc) return;
     const int nv = p.nv, tid = threadIdx.x;
+    const bool aligned = nv % 2 == 0;
     const CellStep<D> cs = cell_step<D>(p, i);
     double2 *tg = reinterpret_cast<double2 *>(smem);
     double *red = smem + (TENSOR ? 2 * p.ntab : 0);
@@ -2567,9 +2515,9 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
     for (int k0 = 2 * tid; k0 < nv; k0 += 2 * BS) {
         double f[NC][2];
         VelPair<D, TENSOR> vp;
-        vp.load(p, k0);
+        vp.load(p, k0, nv, aligned);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) load_pair<FT>(fin + base + (size_t)c * nv, k0, nv, f[c][0], f[c][1]);
+        for (int c = 0; c < NC; ++c) load_pair<FT>(fin + base + (size_t)c * nv, k0, nv, aligned, f[c][0], f[c][1]);
         AT sv[NC][2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -2584,7 +2532,7 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
             add_moments<D>(mom, vp.w[e], c3, c2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
         }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, sv[c][0], sv[c][1]);
+        for (int c = 0; c < NC; ++c) store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, sv[c][0], sv[c][1]);
     }
     wave_sums<NW>(mom);
     if ((tid & 63) == 0)
@@ -2592,6 +2540,45 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
         for (int m = 0; m < NW; ++m) red[(tid >> 6) * NW + m] = mom[m];
     __syncthreads();
     store_base_moments<D, BS>(p, i, red, cs.pn.U);
+}
+
+// The macroscopic update of cell i from the stage-1 moments about U^n, by one
+// wavefront: W^{n+1}, q^{n+1} and the squared change of W to memory, and for
+// the workgroup's pass over f^{n+1} to LDS lam, the prefactors of f+, dt / 2
+// tau (res[0..4)), U and q (then).
+template <int D>
+__device__ __forceinline__ void group_macro(const Params &p, int i, const double (&mm)[Shift<D>::N],
+                                            const double (&Wn)[D + 2], const Prim<D> &pn, double *res)
+{
+    constexpr int NW = D + 2;
+    const int tid = threadIdx.x;
+    double W1[NW], tau1, q1[D];
+    Prim<D> p1;
+    macro_from_shift<D>(p, mm, Wn, pn, p.mom_part + (size_t)i * NW, W1, p1, tau1, q1);
+    if (tid == 0) {
+        res[0] = p1.lam;
+        res[1] = p1.rho * pow_lam_pi<D>(p1.lam);
+        res[2] = 4.0 * (1.0 - p.Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
+        res[3] = 0.5 * p.dt / tau1;
+        bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            res[4 + d] = p1.U[d];
+            res[4 + D + d] = q1[d];
+            p.q[(size_t)i * D + d] = q1[d];
+        }
+#pragma unroll
+        for (int m = 0; m < NW; ++m) {
+            ok = ok && isfinite(W1[m]);
+            p.W[(size_t)i * NW + m] = W1[m];
+            const double dw = W1[m] - Wn[m];
+            p.dW2[(size_t)i * NW + m] = dw * dw;
+        }
+        if (!ok) {
+            atomicOr(p.err, 1);
+            atomicMin(p.err + 1, i);
+        }
+    }
 }
 
 template <int D, typename FT, bool TENSOR, int BS, int NP>
@@ -2603,6 +2590,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
     const int i = xcd_cell(blockIdx.x);
     if (i >= p.nc) return;
     const int tid = threadIdx.x, nv = p.nv;
+    const bool aligned = nv % 2 == 0;
     const size_t base = (size_t)i * NC * nv;
     double2 *tg = reinterpret_cast<double2 *>(smem);  // about U^{n+1}
     double *tc = smem + (TENSOR ? 2 * p.ntab : 0);    // about U^n
@@ -2623,7 +2611,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
             v[j][c][0] = v[j][c][1] = from_f64<AT>(0.0);
             if (k0 < nv) {
                 const AT *q = acc + base + (size_t)c * nv + k0;
-                if (nv & 1) {
+                if (!aligned) {
                     v[j][c][0] = q[0];
                     if (k0 + 1 < nv) v[j][c][1] = q[1];
                 } else {
@@ -2646,7 +2634,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
         const int k0 = 2 * (tid + BS * j);
         if (k0 < nv) {
             VelPair<D, TENSOR> vp;
-            vp.load(p, k0);
+            vp.load(p, k0, nv, aligned);
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 double c[D], c2;
@@ -2665,33 +2653,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
         const double s = tid < N ? group_total<BS, N>(red, tid) : 0.0;
 #pragma unroll
         for (int t = 0; t < N; ++t) mm[t] = read_lane(s, t);
-        double W1[NW], tau1, q1[D];
-        Prim<D> p1;
-        macro_from_shift<D>(p, mm, Wn, pn, p.mom_part + (size_t)i * NW, W1, p1, tau1, q1);
-        if (tid == 0) {
-            res[0] = p1.lam;
-            res[1] = p1.rho * pow_lam_pi<D>(p1.lam);
-            res[2] = 4.0 * (1.0 - p.Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
-            res[3] = 0.5 * p.dt / tau1;
-            bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                res[4 + d] = p1.U[d];
-                res[4 + D + d] = q1[d];
-                p.q[(size_t)i * D + d] = q1[d];
-            }
-#pragma unroll
-            for (int m = 0; m < NW; ++m) {
-                ok = ok && isfinite(W1[m]);
-                p.W[(size_t)i * NW + m] = W1[m];
-                const double dw = W1[m] - Wn[m];
-                p.dW2[(size_t)i * NW + m] = dw * dw;
-            }
-            if (!ok) {
-                atomicOr(p.err, 1);
-                atomicMin(p.err + 1, i);
-            }
-        }
+        group_macro<D>(p, i, mm, Wn, pn, res);
     }
     __syncthreads();
     const double lam = res[0], pref = res[1], shk = res[2], a1 = res[3], inv1 = 1.0 / (1.0 + a1);
@@ -2716,7 +2678,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
         const int k0 = 2 * (tid + BS * j);
         if (k0 < nv) {
             VelPair<D, TENSOR> vp;
-            vp.load(p, k0);
+            vp.load(p, k0, nv, aligned);
             FT fo[NC][2];
             AT bo[NC][2];
 #pragma unroll
@@ -2737,8 +2699,8 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
             }
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                store_pair<FT>(fout + base + (size_t)c * nv, k0, nv, fo[c][0], fo[c][1]);
-                store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, bo[c][0], bo[c][1]);
+                store_pair<FT>(fout + base + (size_t)c * nv, k0, nv, aligned, fo[c][0], fo[c][1]);
+                store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, bo[c][0], bo[c][1]);
             }
         }
     }
@@ -2767,6 +2729,12 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
 // then the base of the next chunk's velocities into the ring, its moments
 // added to mom_part (a chunk index of -1 skips that half; chunk 0 starts
 // each sum).  Each cell's ring slice is touched only by its own workgroup.
+// Bound by a cell's fixed work rather than its bytes at the default chunk (two
+// velocity pairs a thread): the constants come from the prologue, the sums go
+// by lane swaps, the points from the Gaussian table in LDS.  107,118 cells x
+// 4,548 in FP64, a turn of both halves 1.35 -> 0.86 ms, the final kernel
+// below 2.38 -> 1.60 (7.8 GB, 4.9 TB/s), against constants formed by every
+// wavefront of every turn, butterfly sums and points from memory.
 template <int D, typename FT, bool TENSOR>
 __global__ __launch_bounds__(256) void k_push_chunk_turn(Params p, FT *__restrict__ f,
                                                          typename AccOf<FT>::T *__restrict__ ring, int pc0, int pcn,
@@ -2778,72 +2746,107 @@ __global__ __launch_bounds__(256) void k_push_chunk_turn(Params p, FT *__restric
     const int i = xcd_cell(blockIdx.x);
     if (i >= p.nc) return;
     const int nv = p.nv, ch = p.chunk, tid = threadIdx.x;
+    // (chunks start at multiples of ch)
+    const bool aligned = (nv | ch) % 2 == 0;
     const size_t fb = (size_t)i * NC * nv, rb = (size_t)i * NC * ch;
-    double *tb = smem;
-    double *red = smem + (TENSOR ? p.ntab : 0);
-    const CellStep<D> cs = cell_step<D>(p, i);
+    double2 *tg = reinterpret_cast<double2 *>(smem);
+    double *red = smem + (TENSOR ? 2 * p.ntab : 0), *red2 = red + (BS / 64) * N;
+    const CellConst<D> &cs = static_cast<const CellConst<D> *>(p.cconst)[i];
+    double U[D], q[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        U[d] = cs.U[d];
+        q[d] = cs.q[d];
+    }
+    const double lam = cs.lam, pref = cs.pref, shk = cs.shk, hdt_tau = cs.hdt_tau, bh = cs.bh;
+    if constexpr (TENSOR) {
+        fill_gauss<BS>(p, lam, U[0], U[1], U[D - 1], tg);
+        __syncthreads();
+    }
     if (pq >= 0) {
         double mm[N];
 #pragma unroll
         for (int t = 0; t < N; ++t) mm[t] = 0.0;
-#pragma unroll 4
-        for (int kk = tid; kk < pcn; kk += BS) {
-            const int k = pc0 + kk;
-            double v[2] = {0.0, 0.0};
+#pragma unroll 2
+        for (int kk = 2 * tid; kk < pcn; kk += 2 * BS) {
+            VelPair<D, TENSOR> vp;
+            vp.load(p, pc0 + kk, pc0 + pcn, aligned);
+            double v[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 // the moments are taken of the stage-1 value as summed (FP32
                 // for bfloat16 f), as in the two-buffer final kernel
-                const AT x = ring[rb + (size_t)c * ch + kk];
-                if constexpr (sizeof(AT) == sizeof(FT))
-                    f[fb + (size_t)c * nv + k] = x;
-                else
-                    f[fb + (size_t)c * nv + k] = from_f64<FT>(to_f64(x));
-                v[c] = to_f64(x);
+                load_pair<AT>(ring + rb + (size_t)c * ch, kk, pcn, aligned, v[0][c], v[1][c]);
+                store_pair<FT>(f + fb + (size_t)c * nv + pc0, kk, pcn, aligned, from_f64<FT>(v[0][c]),
+                               from_f64<FT>(v[1][c]));
             }
-            double cv[D], c2 = 0.0;
 #pragma unroll
-            for (int d = 0; d < D; ++d) {
-                cv[d] = p.u[d * nv + k] - cs.pn.U[d];
-                c2 = fma(cv[d], cv[d], c2);
+            for (int e = 0; e < 2; ++e) {
+                double c3[D], c2;
+                if constexpr (TENSOR) {
+                    (void)vp.gauss_of(e, tg, U, lam, c3, c2);
+                } else {
+                    vp.peculiar_of(e, nullptr, U, c3, c2);
+                }
+                add_shift_moments<D>(mm, vp.w[e], c3, c2, v[e][0], NC > 1 ? v[e][NC - 1] : 0.0);
             }
-            add_shift_moments<D>(mm, p.w[k], cv, c2, v[0], NC > 1 ? v[NC - 1] : 0.0);
         }
-        block_reduce_wide<BS>(mm, red, OpAdd{});
-        if (tid == 0)
+        wave_sums<N>(mm);
+        if ((tid & 63) == 0)
 #pragma unroll
-            for (int t = 0; t < N; ++t)
-                p.mom_s[(size_t)i * N + t] = (pq == 0 ? 0.0 : p.mom_s[(size_t)i * N + t]) + mm[t];
+            for (int t = 0; t < N; ++t) red[(tid >> 6) * N + t] = mm[t];
     }
     if (nq >= 0) {
-        if constexpr (TENSOR) fill_group_table<D, BS>(p, cs.pn.lam, cs.pn.U[0], cs.pn.U[1], cs.pn.U[D - 1], tb);
         double mom[NW];
 #pragma unroll
         for (int m = 0; m < NW; ++m) mom[m] = 0.0;
 #pragma unroll 2
-        for (int kk = tid; kk < ncn; kk += BS) {
-            const int k = nc0 + kk;
-            double u[D], u2;
-            velocity<D>(p, k, u, u2);
-            const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-            double fp[2];
-            const double H = cs.pref_n * own_gauss<D, TENSOR>(p, tb, kx, u, cs.pn.lam, cs.pn.U);
-            shakhov<D>(u, cs.pn.U, cs.pn.lam, cs.shk_n, cs.qn, cs.bh_n, H, fp[0], fp[1]);
-            double bv[2] = {0.0, 0.0};
+        for (int kk = 2 * tid; kk < ncn; kk += 2 * BS) {
+            VelPair<D, TENSOR> vp;
+            vp.load(p, nc0 + kk, nc0 + ncn, aligned);
+            double fv[NC][2];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const double fv = to_f64(f[fb + (size_t)c * nv + k]);
-                const AT sv = from_f64<AT>(fma(cs.hdt_tau, fp[c] - fv, fv));
-                ring[rb + (size_t)c * ch + kk] = sv;
-                bv[c] = to_f64(sv);
+            for (int c = 0; c < NC; ++c)
+                load_pair<FT>(f + fb + (size_t)c * nv + nc0, kk, ncn, aligned, fv[c][0], fv[c][1]);
+            AT sv[NC][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                double c3[D], c2, fp[2], bv[2] = {0.0, 0.0};
+                const double H = pref * vp.gauss_of(e, tg, U, lam, c3, c2);
+                shakhov_at<D>(c3, c2, lam, shk, q, bh, H, fp[0], fp[1]);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    sv[c][e] = from_f64<AT>(fma(hdt_tau, fp[c] - fv[c][e], fv[c][e]));
+                    bv[c] = to_f64(sv[c][e]);
+                }
+                add_moments<D>(mom, vp.w[e], c3, c2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
             }
-            add_moments<D>(mom, p.w[k], u, u2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
-        }
-        block_reduce_wide<BS>(mom, red, OpAdd{});
-        if (tid == 0)
 #pragma unroll
-            for (int m = 0; m < NW; ++m)
-                p.mom_part[(size_t)i * NW + m] = (nq == 0 ? 0.0 : p.mom_part[(size_t)i * NW + m]) + mom[m];
+            for (int c = 0; c < NC; ++c)
+                store_pair<AT>(ring + rb + (size_t)c * ch, kk, ncn, aligned, sv[c][0], sv[c][1]);
+        }
+        wave_sums<NW>(mom);
+        if ((tid & 63) == 0)
+#pragma unroll
+            for (int m = 0; m < NW; ++m) red2[(tid >> 6) * NW + m] = mom[m];
+    }
+    __syncthreads();
+    // the chunks' sums, in chunk order
+    if (pq >= 0 && tid < N) {
+        double *m = p.mom_s + (size_t)i * N + tid;
+        *m = (pq == 0 ? 0.0 : *m) + group_total<BS, N>(red, tid);
+    }
+    if (nq >= 0 && tid >= 64 && tid < 128) {
+        const int n = tid - 64;
+        const double s = n < NW ? group_total<BS, NW>(red2, n) : 0.0;
+        double m[NW];
+#pragma unroll
+        for (int t = 0; t < NW; ++t) m[t] = read_lane(s, t);
+        const double r = recentred<D>(m, U, n);
+        if (n < NW) {
+            double *mp = p.mom_part + (size_t)i * NW + n;
+            *mp = (nq == 0 ? 0.0 : *mp) + r;
+        }
     }
 }
 
@@ -2856,53 +2859,50 @@ __global__ __launch_bounds__(256) void k_push_final_inplace(Params p, FT *__rest
     const int i = xcd_cell(blockIdx.x);
     if (i >= p.nc) return;
     const int nv = p.nv, tid = threadIdx.x;
-    const double dt = p.dt, Pr = p.Pr;
-    double Wn[NW];
+    const bool aligned = nv % 2 == 0;
+    double2 *tg = reinterpret_cast<double2 *>(smem);
+    double *res = smem + (TENSOR ? 2 * p.ntab : 0);
+    if (tid < 64) {
+        double Wn[NW], mm[N];
 #pragma unroll
-    for (int m = 0; m < NW; ++m) Wn[m] = p.W[(size_t)i * NW + m];
-    const Prim<D> pn = to_prim<D>(Wn);
-    double mm[N];
+        for (int m = 0; m < NW; ++m) Wn[m] = p.W[(size_t)i * NW + m];
+        const Prim<D> pn = to_prim<D>(Wn);
 #pragma unroll
-    for (int t = 0; t < N; ++t) mm[t] = p.mom_s[(size_t)i * N + t];
-    double W1[NW], tau1, q1[D];
-    Prim<D> p1;
-    macro_from_shift<D>(p, mm, Wn, pn, p.mom_part + (size_t)i * NW, W1, p1, tau1, q1);
-    double *tb = smem;
-    if constexpr (TENSOR) fill_group_table<D, BS>(p, p1.lam, p1.U[0], p1.U[1], p1.U[D - 1], tb);
-    const double pref_1 = p1.rho * pow_lam_pi<D>(p1.lam);
-    const double shk_1 = 4.0 * (1.0 - Pr) * p1.lam * p1.lam / (5.0 * p1.rho);
-    const double a1 = 0.5 * dt / tau1, inv1 = 1.0 / (1.0 + a1);
-    const double bh_1 = Dim<D>::M / (2.0 * p1.lam);
-    const size_t fb = (size_t)i * NC * nv;
-#pragma unroll 2
-    for (int k = tid; k < nv; k += BS) {
-        double u[D], u2;
-        velocity<D>(p, k, u, u2);
-        const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
-        double fp[2];
-        const double H = pref_1 * own_gauss<D, TENSOR>(p, tb, kx, u, p1.lam, p1.U);
-        shakhov<D>(u, p1.U, p1.lam, shk_1, q1, bh_1, H, fp[0], fp[1]);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            FT *q = f + fb + (size_t)c * nv + k;
-            *q = from_f64<FT>((to_f64(*q) + a1 * fp[c]) * inv1);
-        }
+        for (int t = 0; t < N; ++t) mm[t] = p.mom_s[(size_t)i * N + t];
+        group_macro<D>(p, i, mm, Wn, pn, res);
     }
-    if (tid == 0) {
-        bool ok = p1.rho > 0.0 && p1.lam > 0.0 && isfinite(p1.rho) && isfinite(p1.lam);
+    __syncthreads();
+    const double lam = res[0], pref = res[1], shk = res[2], a1 = res[3], inv1 = 1.0 / (1.0 + a1);
+    const double bh = Dim<D>::M / (2.0 * lam);
+    double U[D], q1[D];
 #pragma unroll
-        for (int m = 0; m < NW; ++m) {
-            ok = ok && isfinite(W1[m]);
-            p.W[(size_t)i * NW + m] = W1[m];
-            const double dw = W1[m] - Wn[m];
-            p.dW2[(size_t)i * NW + m] = dw * dw;
+    for (int d = 0; d < D; ++d) {
+        U[d] = res[4 + d];
+        q1[d] = res[4 + D + d];
+    }
+    if constexpr (TENSOR) {
+        fill_gauss<BS>(p, lam, U[0], U[1], U[D - 1], tg);
+        __syncthreads();
+    }
+    const size_t fb = (size_t)i * NC * nv;
+#pragma unroll 4
+    for (int k0 = 2 * tid; k0 < nv; k0 += 2 * BS) {
+        VelPair<D, TENSOR> vp;
+        vp.load(p, k0, nv, aligned);
+        double v[NC][2];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) load_pair<FT>(f + fb + (size_t)c * nv, k0, nv, aligned, v[c][0], v[c][1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            double c3[D], c2, fp[2];
+            const double H = pref * vp.gauss_of(e, tg, U, lam, c3, c2);
+            shakhov_at<D>(c3, c2, lam, shk, q1, bh, H, fp[0], fp[1]);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[c][e] = (v[c][e] + a1 * fp[c]) * inv1;
         }
 #pragma unroll
-        for (int d = 0; d < D; ++d) p.q[(size_t)i * D + d] = q1[d];
-        if (!ok) {
-            atomicOr(p.err, 1);
-            atomicMin(p.err + 1, i);
-        }
+        for (int c = 0; c < NC; ++c)
+            store_pair<FT>(f + fb + (size_t)c * nv, k0, nv, aligned, from_f64<FT>(v[c][0]), from_f64<FT>(v[c][1]));
     }
 }
 
@@ -2994,7 +2994,8 @@ hipError_t push_inplace_t(const Params &p, void *fv, const int *cells, const int
     const size_t tab = sizeof(double) * (size_t)(MF + 1) * (TENSOR ? p.ntab : 0);
     const size_t red = sizeof(double) * ((BS / 64) * (2 * NW + 2) + MF);
     const unsigned gc = (unsigned)sweep_grid(p.nc);
-    const size_t lcell = sizeof(double) * ((TENSOR ? (size_t)p.ntab : 0) + 5 * 16);
+    const size_t tg = sizeof(double) * (TENSOR ? 2 * (size_t)p.ntab : 0);
+    const size_t lturn = tg + sizeof(double) * (BS / 64) * (Shift<D>::N + NW), lfin = tg + sizeof(double) * (4 + 2 * D);
     if (n_wall_cells > 0)
         hipLaunchKernelGGL((k_push_wall<D, FT, BS, TENSOR>), dim3(n_wall_cells), dim3(BS), tab + red, s, p, f,
                            wall_cells, n_wall_cells);
@@ -3002,7 +3003,7 @@ hipError_t push_inplace_t(const Params &p, void *fv, const int *cells, const int
         const int c0 = q * p.chunk, cn = std::min(p.chunk, p.nv - c0);
         // the previous chunk back into f, this chunk's base into the ring
         const int pc0 = (q - 1) * p.chunk;
-        hipLaunchKernelGGL((k_push_chunk_turn<D, FT, TENSOR>), dim3(gc), dim3(BS), lcell, s, p, f, ring, pc0,
+        hipLaunchKernelGGL((k_push_chunk_turn<D, FT, TENSOR>), dim3(gc), dim3(BS), lturn, s, p, f, ring, pc0,
                            q > 0 ? p.chunk : 0, q - 1, c0, cn, q);
         for (int c = 0; c < ncol; ++c) {
             const int n = coff[c + 1] - coff[c];
@@ -3020,10 +3021,10 @@ hipError_t push_inplace_t(const Params &p, void *fv, const int *cells, const int
     }
     {
         const int q = p.nchunk - 1, c0 = q * p.chunk;
-        hipLaunchKernelGGL((k_push_chunk_turn<D, FT, TENSOR>), dim3(gc), dim3(BS), lcell, s, p, f, ring, c0,
+        hipLaunchKernelGGL((k_push_chunk_turn<D, FT, TENSOR>), dim3(gc), dim3(BS), lturn, s, p, f, ring, c0,
                            p.nv - c0, q, 0, 0, -1);
     }
-    hipLaunchKernelGGL((k_push_final_inplace<D, FT, TENSOR>), dim3(gc), dim3(BS), lcell, s, p, f);
+    hipLaunchKernelGGL((k_push_final_inplace<D, FT, TENSOR>), dim3(gc), dim3(BS), lfin, s, p, f);
     return hipGetLastError();
 }
 
