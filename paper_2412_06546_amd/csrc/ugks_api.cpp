@@ -1406,8 +1406,8 @@ int batch_layout(ugks_t *const *hs, int n, BatchItem *items, int *off, int *orde
         items[j].f[1] = h->f[1];
         items[j].res = h->res;
         items[j].cur = h->cur;
-        og[j + 1] = og[j] + (h->nc + 255) / 256;
-        of[j + 1] = of[j] + (h->nf + 127) / 128;
+        og[j + 1] = og[j] + (h->nc + kGradBlock - 1) / kGradBlock;
+        of[j + 1] = of[j] + (h->nf + kFaceBlock - 1) / kFaceBlock;
     }
     int ng = 0;
     size_t at = 0;

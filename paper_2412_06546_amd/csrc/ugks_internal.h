@@ -133,6 +133,14 @@ constexpr size_t kStaticItemsBytes = ((sizeof(BatchItem) * kStaticBatchMax + 255
 constexpr size_t kStaticScratchBytes = kStaticItemsBytes + sizeof(int) * (4 * kStaticBatchMax + 3);
 hipError_t static_scratch(void **out);
 
+// Threads per workgroup of the prologue's kernels, a thread per cell and per
+// face: one wavefront.  Every lane reads a record of hundreds of bytes, so
+// the kernels are bound by the address units of the CUs that they reach:
+// gradients of 2,197 cells in 3D 18.7 us with 256 threads, 13.8 with 64; of
+// 1,058,685 cells 1.44 ms with 256 threads and a division per face and
+// component, 0.93 now; interface records of 2,197 cells 9.6 -> 6.8 us.
+constexpr int kGradBlock = 64, kFaceBlock = 64;
+
 // Dynamic LDS of the sweep for one case, and whether its stage-1 values
 // stay in LDS (s1l).
 size_t sweep_lds_bytes(const Params &p, bool *s1l);

@@ -564,31 +564,43 @@ __device__ __forceinline__ void cell_grad(const Params p, int i)
     double gr[NW][D];
 #pragma unroll
     for (int m = 0; m < NW; ++m) {
-        double mx = Wi[m], mn = Wi[m];
+        double up = 0.0, dn = 0.0;  // extremes of W_j - W_i (0 for the cell itself)
 #pragma unroll
         for (int d = 0; d < D; ++d) gr[m][d] = 0.0;
 #pragma unroll
         for (int j = 0; j < MF; ++j) {
             if (j >= nf) break;
-            const double wj = Wn[j][m];
+            const double df = Wn[j][m] - Wi[m];
 #pragma unroll
-            for (int d = 0; d < D; ++d) gr[m][d] += g.lsq[j][d] * (wj - Wi[m]);
-            mx = fmax(mx, wj);
-            mn = fmin(mn, wj);
+            for (int d = 0; d < D; ++d) gr[m][d] += g.lsq[j][d] * df;
+            up = fmax(up, df);
+            dn = fmin(dn, df);
         }
         if (p.limiter) {
-            double phi = 1.0;
+            // the two extreme face increments decide (as for f, slope_from);
+            // one division a component where every face took one
+            double hi = 0.0, lo = 0.0;
 #pragma unroll
             for (int j = 0; j < MF; ++j) {
                 if (j >= nf) break;
                 double dm = 0.0;
 #pragma unroll
                 for (int d = 0; d < D; ++d) dm += gr[m][d] * g.dvec[j][d];
-                if (dm == 0.0) continue;
-                double dp = dm > 0.0 ? mx - Wi[m] : mn - Wi[m];
-                double ph = (dp * dp + g.eps2 + 2.0 * dm * dp) / (dp * dp + 2.0 * dm * dm + dm * dp + g.eps2);
-                phi = fmin(phi, ph);
+                hi = fmax(hi, dm);
+                lo = fmin(lo, dm);
             }
+            const double nu = up * up + g.eps2 + 2.0 * hi * up, du = up * up + 2.0 * hi * hi + hi * up + g.eps2;
+            const double nd = dn * dn + g.eps2 + 2.0 * lo * dn, dd = dn * dn + 2.0 * lo * lo + lo * dn + g.eps2;
+            double bn = 1.0, bd = 1.0;
+            if (hi > 0.0 && nu < du) {
+                bn = nu;
+                bd = du;
+            }
+            if (lo < 0.0 && nd * bd < bn * dd) {
+                bn = nd;
+                bd = dd;
+            }
+            const double phi = bn / bd;
 #pragma unroll
             for (int d = 0; d < D; ++d) gr[m][d] *= phi;
         }
@@ -607,7 +619,8 @@ __device__ __forceinline__ void cell_grad(const Params p, int i)
         }
 #pragma unroll
         for (int d = 0; d < D; ++d) ke += Wf[1 + d] * Wf[1 + d];
-        if (!(Wf[0] > 0.0) || !(Wf[NW - 1] - 0.5 * ke / Wf[0] > 0.0)) bad = true;
+        // rho E > |rho U|^2 / 2, both sides of E > rho U^2 / 2 times rho > 0
+        if (!(Wf[0] > 0.0) || !(Wf[NW - 1] * Wf[0] - 0.5 * ke > 0.0)) bad = true;
     }
 #pragma unroll
     for (int m = 0; m < NW; ++m)
@@ -616,9 +629,9 @@ __device__ __forceinline__ void cell_grad(const Params p, int i)
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_cell_grad(Params p)
+__global__ __launch_bounds__(kGradBlock) void k_cell_grad(Params p)
 {
-    cell_grad<D>(p, blockIdx.x * 256 + threadIdx.x);
+    cell_grad<D>(p, blockIdx.x * kGradBlock + threadIdx.x);
 }
 
 // ------------------------------------------------------------------------
@@ -626,10 +639,10 @@ __global__ __launch_bounds__(256) void k_cell_grad(Params p)
 // ------------------------------------------------------------------------
 // Slopes of a Maxwellian in its own frame: with c = u - U, a quantity
 // a . (1, c, (|c|^2 + |xi|^2) / 2) with <(1, c, ..) (a . (1, c, ..))>_g = Delta
-// for the rho-normalised moments of g (N = 3 degrees of freedom), s = 1 / (2 lam);
+// for the rho-normalised moments of g (N = 3 degrees of freedom), s = 1 / (2 lam), is = 1 / s;
 // Dl holds Delta for (1, u, |u|^2 / 2 + |xi|^2 / 2), as a gradient of W / rho is given.
 template <int D>
-__device__ __forceinline__ void slope_solve(const double (&U)[D], double s, const double *Dl, double (&a)[D + 2])
+__device__ __forceinline__ void slope_solve(const double (&U)[D], double s, double is, const double *Dl, double (&a)[D + 2])
 {
     constexpr int NW = D + 2;
     double U2 = 0.0, Um = 0.0;
@@ -637,10 +650,10 @@ __device__ __forceinline__ void slope_solve(const double (&U)[D], double s, cons
     for (int d = 0; d < D; ++d) {
         U2 = fma(U[d], U[d], U2);
         Um = fma(U[d], Dl[1 + d], Um);
-        a[1 + d] = (Dl[1 + d] - U[d] * Dl[0]) / s;
+        a[1 + d] = (Dl[1 + d] - U[d] * Dl[0]) * is;
     }
     const double De = Dl[NW - 1] - Um + 0.5 * U2 * Dl[0];
-    a[NW - 1] = (De - 0.5 * N_DOF * s * Dl[0]) / (0.5 * N_DOF * s * s);
+    a[NW - 1] = (De - 0.5 * N_DOF * s * Dl[0]) * (2.0 / N_DOF * is * is);
     a[0] = Dl[0] - 0.5 * N_DOF * s * a[NW - 1];
 }
 
@@ -650,7 +663,7 @@ __device__ __forceinline__ void slope_solve(const double (&U)[D], double s, cons
 // moments <c_i c_j> = s, <e> = N s / 2, <c_i c_j e> = (N + 2) s^2 / 2,
 // <e^2> = N (N + 2) s^2 / 4, then the same solve.
 template <int D>
-__device__ __forceinline__ void time_slope(const double (&U)[D], double s, const double (&a)[D][D + 2],
+__device__ __forceinline__ void time_slope(const double (&U)[D], double s, double is, const double (&a)[D][D + 2],
                                            double (&A)[D + 2])
 {
     constexpr int NW = D + 2, N = N_DOF;
@@ -666,37 +679,45 @@ __device__ __forceinline__ void time_slope(const double (&U)[D], double s, const
         for (int b = 0; b < D; ++b) rb[b] -= s * U[d] * a[d][1 + b];
     }
 #pragma unroll
-    for (int b = 0; b < D; ++b) A[1 + b] = rb[b] / s;
-    A[NW - 1] = (re - 0.5 * N * s * r0) / (0.5 * N * s * s);
+    for (int b = 0; b < D; ++b) A[1 + b] = rb[b] * is;
+    A[NW - 1] = (re - 0.5 * N * s * r0) * (2.0 / N * is * is);
     A[0] = r0 - 0.5 * N * s * A[NW - 1];
 }
 
-__device__ void time_integrals(double dt, double tau, double *c)
+__device__ __forceinline__ void time_integrals(double dt, double tau, double *c)
 {
     const double x = dt / tau;
     if (x < 1.0) {
-        // Taylor series (the closed forms cancel catastrophically for small x)
-        double term[31];
-        term[0] = 1.0;
-        for (int m = 1; m <= 30; ++m) term[m] = term[m - 1] * x / m;
+        // Taylor series (the closed forms cancel catastrophically for small
+        // x): with e_m = (-1)^(m+1) / m!,
+        //   sum_{m>=1} e_m x^m, sum_{m>=2} (m-1) e_m x^m, -sum_{m>=2} e_m x^m,
+        //   -sum_{m>=3} (m-2) e_m x^m, sum_{m>=3} e_m x^m
+        // by Horner's rule, without their leading powers of x.  The terms left
+        // out after m = 22 are below 1e-19 of the first.
+        constexpr int M = 22;
+        double inv = 1.0;
+#pragma unroll
+        for (int m = 2; m <= M; ++m) inv /= m;  // 1 / M!, folded at compile time
         double s1 = 0, s2 = 0, s3 = 0, s4 = 0, s5 = 0;
-        for (int m = 30; m >= 1; --m) {
-            const double t = (m & 1) ? term[m] : -term[m];
-            s1 += t;
+#pragma unroll
+        for (int m = M; m >= 1; --m) {
+            const double e = (m & 1) ? inv : -inv;
+            s1 = fma(s1, x, e);
             if (m >= 2) {
-                s2 += (m - 1) * t;
-                s3 -= t;
+                s2 = fma(s2, x, (m - 1) * e);
+                s3 = fma(s3, x, -e);
             }
             if (m >= 3) {
-                s4 -= (m - 2) * t;
-                s5 += t;
+                s4 = fma(s4, x, -(m - 2) * e);
+                s5 = fma(s5, x, e);
             }
+            inv *= m;
         }
-        c[0] = tau * s1;
-        c[1] = tau * tau * s2;
-        c[2] = tau * s3;
-        c[3] = tau * tau * s4;
-        c[4] = tau * tau * s5;
+        c[0] = dt * s1;              // tau x = dt
+        c[1] = dt * dt * s2;
+        c[2] = dt * x * s3;
+        c[3] = dt * dt * x * s4;
+        c[4] = dt * dt * x * s5;
     } else {
         const double e = exp(-x), ome = -expm1(-x);
         c[0] = tau * ome;
@@ -738,15 +759,24 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
         return;
     }
     // reconstructed states on both sides
-    double Wl[NW], Wr[NW];
+    double Wl[NW], Wr[NW], gl[NW][D], gr[NW][D];
+#pragma unroll
     for (int m = 0; m < NW; ++m) {
         Wl[m] = p.W[(size_t)F.l * NW + m];
         Wr[m] = p.W[(size_t)F.r * NW + m];
+#pragma unroll
         for (int d = 0; d < D; ++d) {
-            Wl[m] += p.gW[((size_t)F.l * NW + m) * D + d] * F.dl[d];
-            Wr[m] += p.gW[((size_t)F.r * NW + m) * D + d] * F.dr[d];
+            gl[m][d] = p.gW[((size_t)F.l * NW + m) * D + d];
+            gr[m][d] = p.gW[((size_t)F.r * NW + m) * D + d];
         }
     }
+#pragma unroll
+    for (int m = 0; m < NW; ++m)
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            Wl[m] += gl[m][d] * F.dl[d];
+            Wr[m] += gr[m][d] * F.dr[d];
+        }
     // W0 from the two half-Maxwellians in the face-normal frame
     double W0[NW];
     for (int m = 0; m < NW; ++m) W0[m] = 0.0;
@@ -775,7 +805,7 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
         W0[NW - 1] += 0.5 * pr.rho * (m2 + (ut2 + (N_DOF - 1) / (2.0 * pr.lam)) * m0);
     }
     const Prim<D> p0 = to_prim<D>(W0);
-    const double s = 1.0 / (2.0 * p0.lam);
+    const double is = 2.0 * p0.lam, s = 1.0 / is, half_rho = 0.5 / p0.rho;
     // spatial slopes from the averaged limited gradients, the time slope
     double a[D][NW], A[NW], q[D], c[5];
 #pragma unroll
@@ -783,11 +813,11 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
         double Dl[NW];
 #pragma unroll
         for (int m = 0; m < NW; ++m)
-            Dl[m] = 0.5 * (p.gW[((size_t)F.l * NW + m) * D + d] + p.gW[((size_t)F.r * NW + m) * D + d]) / p0.rho;
-        slope_solve<D>(p0.U, s, Dl, a[d]);
+            Dl[m] = half_rho * (gl[m][d] + gr[m][d]);
+        slope_solve<D>(p0.U, s, is, Dl, a[d]);
         q[d] = 0.5 * (p.q[(size_t)F.l * D + d] + p.q[(size_t)F.r * D + d]);
     }
-    time_slope<D>(p0.U, s, a, A);
+    time_slope<D>(p0.U, s, is, a, A);
     time_integrals(p.dt, collision_time(p0.rho, p0.lam, p.mu_ref, p.omega), c);
     // the cubic in c: c[2] (1 + Shakhov) + c[3] u . a + c[4] A.  Integrated
     // over xi the energy moment (|c|^2 + |xi|^2) / 2 becomes
@@ -829,9 +859,9 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
 }
 
 template <int D>
-__global__ __launch_bounds__(128) void k_face_eq(Params p)
+__global__ __launch_bounds__(kFaceBlock) void k_face_eq(Params p)
 {
-    face_eq<D>(p, blockIdx.x * 128 + threadIdx.x);
+    face_eq<D>(p, blockIdx.x * kFaceBlock + threadIdx.x);
 }
 
 // ------------------------------------------------------------------------
@@ -1957,7 +1987,7 @@ __device__ __forceinline__ void residual(const Params p, double *out)
 // in order and takes the square roots.  Deterministic, and spread over the
 // chip instead of one compute unit.
 template <int D>
-__global__ __launch_bounds__(256) void k_residual_part(Params p, double *part, int per)
+__global__ __launch_bounds__(256) void k_residual_part(Params p, double *part, int per, double *out)
 {
     constexpr int NW = D + 2;
     __shared__ double lds[4 * NW];
@@ -1971,7 +2001,10 @@ __global__ __launch_bounds__(256) void k_residual_part(Params p, double *part, i
     block_reduce<256>(s, lds, OpAdd{});
     if (threadIdx.x == 0)
 #pragma unroll
-        for (int m = 0; m < NW; ++m) part[(size_t)blockIdx.x * NW + m] = s[m];
+        for (int m = 0; m < NW; ++m) {
+            part[(size_t)blockIdx.x * NW + m] = s[m];
+            if (gridDim.x == 1) out[m] = sqrt(s[m]);  // the only group: no second launch
+        }
 }
 
 template <int D>
@@ -2019,19 +2052,19 @@ __device__ __forceinline__ int batch_case(const int *__restrict__ off, int n, in
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void k_cell_grad_batch(const BatchItem *__restrict__ items, const int *__restrict__ off,
+__global__ __launch_bounds__(kGradBlock) void k_cell_grad_batch(const BatchItem *__restrict__ items, const int *__restrict__ off,
                                                          int n)
 {
     const int c = batch_case(off, n, blockIdx.x);
-    cell_grad<D>(((ConstItems)items)[c].p, (blockIdx.x - off[c]) * 256 + threadIdx.x);
+    cell_grad<D>(((ConstItems)items)[c].p, (blockIdx.x - off[c]) * kGradBlock + threadIdx.x);
 }
 
 template <int D>
-__global__ __launch_bounds__(128) void k_face_eq_batch(const BatchItem *__restrict__ items, const int *__restrict__ off,
+__global__ __launch_bounds__(kFaceBlock) void k_face_eq_batch(const BatchItem *__restrict__ items, const int *__restrict__ off,
                                                        int n)
 {
     const int c = batch_case(off, n, blockIdx.x);
-    face_eq<D>(((ConstItems)items)[c].p, (blockIdx.x - off[c]) * 128 + threadIdx.x);
+    face_eq<D>(((ConstItems)items)[c].p, (blockIdx.x - off[c]) * kFaceBlock + threadIdx.x);
 }
 
 template <int D, typename FT, int BS, bool TENSOR, bool S1L>
@@ -2108,8 +2141,8 @@ hipError_t launch_moments(const Params &p, const void *f, hipStream_t s)
 
 template <int D> hipError_t prologue_d(const Params &p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cell_grad<D>, dim3((p.nc + 255) / 256), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(k_face_eq<D>, dim3((p.nf + 127) / 128), dim3(128), 0, s, p);
+    hipLaunchKernelGGL(k_cell_grad<D>, dim3((p.nc + kGradBlock - 1) / kGradBlock), dim3(kGradBlock), 0, s, p);
+    hipLaunchKernelGGL(k_face_eq<D>, dim3((p.nf + kFaceBlock - 1) / kFaceBlock), dim3(kFaceBlock), 0, s, p);
     return hipGetLastError();
 }
 hipError_t launch_prologue(const Params &p, hipStream_t s)
@@ -3130,11 +3163,11 @@ hipError_t launch_batch_prologue(const BatchItem *items, int n, const int *off_g
                                  const int *off_face, int grid_face, int dim, hipStream_t s)
 {
     if (dim == 2) {
-        hipLaunchKernelGGL(k_cell_grad_batch<2>, dim3(grid_grad), dim3(256), 0, s, items, off_grad, n);
-        hipLaunchKernelGGL(k_face_eq_batch<2>, dim3(grid_face), dim3(128), 0, s, items, off_face, n);
+        hipLaunchKernelGGL(k_cell_grad_batch<2>, dim3(grid_grad), dim3(kGradBlock), 0, s, items, off_grad, n);
+        hipLaunchKernelGGL(k_face_eq_batch<2>, dim3(grid_face), dim3(kFaceBlock), 0, s, items, off_face, n);
     } else {
-        hipLaunchKernelGGL(k_cell_grad_batch<3>, dim3(grid_grad), dim3(256), 0, s, items, off_grad, n);
-        hipLaunchKernelGGL(k_face_eq_batch<3>, dim3(grid_face), dim3(128), 0, s, items, off_face, n);
+        hipLaunchKernelGGL(k_cell_grad_batch<3>, dim3(grid_grad), dim3(kGradBlock), 0, s, items, off_grad, n);
+        hipLaunchKernelGGL(k_face_eq_batch<3>, dim3(grid_face), dim3(kFaceBlock), 0, s, items, off_face, n);
     }
     return hipGetLastError();
 }
@@ -3220,11 +3253,11 @@ hipError_t launch_residual(const Params &p, double *out, hipStream_t s)
     const int ng = residual_groups(p.nc), per = (p.nc + ng - 1) / ng;
     double *part = out + (p.dim + 2);
     if (p.dim == 2) {
-        hipLaunchKernelGGL(k_residual_part<2>, dim3(ng), dim3(256), 0, s, p, part, per);
-        hipLaunchKernelGGL(k_residual_final<2>, dim3(1), dim3(256), 0, s, part, ng, out);
+        hipLaunchKernelGGL(k_residual_part<2>, dim3(ng), dim3(256), 0, s, p, part, per, out);
+        if (ng > 1) hipLaunchKernelGGL(k_residual_final<2>, dim3(1), dim3(256), 0, s, part, ng, out);
     } else {
-        hipLaunchKernelGGL(k_residual_part<3>, dim3(ng), dim3(256), 0, s, p, part, per);
-        hipLaunchKernelGGL(k_residual_final<3>, dim3(1), dim3(256), 0, s, part, ng, out);
+        hipLaunchKernelGGL(k_residual_part<3>, dim3(ng), dim3(256), 0, s, p, part, per, out);
+        if (ng > 1) hipLaunchKernelGGL(k_residual_final<3>, dim3(1), dim3(256), 0, s, part, ng, out);
     }
     return hipGetLastError();
 }
