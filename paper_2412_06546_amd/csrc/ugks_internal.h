@@ -70,8 +70,8 @@ template <int D> struct alignas(16) FaceEq {
 // A cell's constants at t^n for the streaming kernels of the push sweep in
 // place, which visit every cell once per velocity chunk: written once a step
 // by the prologue.
-template <int D> struct alignas(16) CellConst {
-    double U[D], lam, pref, shk, q[D], hdt_tau, bh;
+template <int D> struct CellConst {
+    double U[D], lam, pref, shk, hdt_tau;
 };
 
 struct Params {

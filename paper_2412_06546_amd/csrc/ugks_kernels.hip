@@ -529,15 +529,11 @@ template <int D> __device__ __forceinline__ CellConst<D> cell_const(const Params
     const Prim<D> pn = to_prim<D>(p.W + (size_t)i * (D + 2));
     CellConst<D> c;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        c.U[d] = pn.U[d];
-        c.q[d] = p.q[(size_t)i * D + d];
-    }
+    for (int d = 0; d < D; ++d) c.U[d] = pn.U[d];
     c.lam = pn.lam;
     c.pref = pn.rho * pow_lam_pi<D>(pn.lam);
     c.shk = 4.0 * (1.0 - p.Pr) * pn.lam * pn.lam / (5.0 * pn.rho);
     c.hdt_tau = 0.5 * p.dt / collision_time(pn.rho, pn.lam, p.mu_ref, p.omega);
-    c.bh = Dim<D>::M / (2.0 * pn.lam);
     return c;
 }
 
@@ -2789,9 +2785,9 @@ __global__ __launch_bounds__(256) void k_push_chunk_turn(Params p, FT *__restric
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         U[d] = cs.U[d];
-        q[d] = cs.q[d];
+        q[d] = p.q[(size_t)i * D + d];
     }
-    const double lam = cs.lam, pref = cs.pref, shk = cs.shk, hdt_tau = cs.hdt_tau, bh = cs.bh;
+    const double lam = cs.lam, pref = cs.pref, shk = cs.shk, hdt_tau = cs.hdt_tau, bh = Dim<D>::M / (2.0 * lam);
     if constexpr (TENSOR) {
         fill_gauss<BS>(p, lam, U[0], U[1], U[D - 1], tg);
         __syncthreads();
