@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -61,10 +62,14 @@ struct ugks {
     long prof_n = 0;
     std::vector<int> perm;     // stored velocity index -> caller's index
     std::vector<int> cell_of;  // stored cell index -> caller's index
-    // asynchronous stepping: pinned copies of the error flag and residual,
-    // and an event marking the end of the last enqueued steps
-    int *h_err = nullptr;
-    double *h_res = nullptr;
+    // the error flag (2 ints) and the residual behind it lie together on the
+    // device (stat), so that one copy brings both into pinned memory: h_err
+    // and h_res for the asynchronous steps, s_err and s_res for ugks_step
+    double *stat = nullptr, *h_stat = nullptr;
+    int *h_err = nullptr, *s_err = nullptr;
+    double *h_res = nullptr, *s_res = nullptr;
+    double *h_macro = nullptr;  // pinned staging of W and q (small cases), behind h_stat
+    // an event marking the end of the last enqueued steps
     hipEvent_t done_ev = nullptr;
     int pending = 0;
 };
@@ -584,13 +589,24 @@ std::string nonphysical_message(const ugks_t *h, int stored)
     return "non-physical state (rho <= 0, T <= 0 or non-finite) at cell " + std::to_string(c);
 }
 
-// pinned copies of the flag and residual, and the completion event, for
-// asynchronous stepping (allocated on first use)
+// W and q of at most this many values (1 MiB) are read out through pinned
+// memory: a pageable copy of a few kilobytes took as long as a step of a small
+// case (400 cells: ugks_macros 43 -> 13 us)
+constexpr size_t kMacroPinned = 1u << 17;
+
+// pinned copies of the flag and residual, the staging of W and q, and the
+// completion event (allocated on first use)
 void ensure_async(ugks_t *h)
 {
     if (h->h_err) return;
-    hip_check(hipHostMalloc((void **)&h->h_err, 2 * sizeof(int), hipHostMallocDefault), "hipHostMalloc");
-    hip_check(hipHostMalloc((void **)&h->h_res, (h->dim + 2) * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+    const size_t n = 1 + (size_t)(h->dim + 2);
+    const size_t macro = (size_t)h->nc * (2 * h->dim + 2), staged = macro <= kMacroPinned ? macro : 0;
+    hip_check(hipHostMalloc((void **)&h->h_stat, (2 * n + staged) * sizeof(double), hipHostMallocDefault), "hipHostMalloc");
+    h->h_macro = staged ? h->h_stat + 2 * n : nullptr;
+    h->h_err = reinterpret_cast<int *>(h->h_stat);
+    h->h_res = h->h_stat + 1;
+    h->s_err = reinterpret_cast<int *>(h->h_stat + n);
+    h->s_res = h->h_stat + n + 1;
     hip_check(hipEventCreateWithFlags(&h->done_ev, hipEventDisableTiming), "hipEventCreate");
 }
 
@@ -598,20 +614,18 @@ void ensure_async(ugks_t *h)
 // memory, mark the end, and leave the handle pending until ugks_poll
 void finish_async(ugks_t *h)
 {
-    hip_check(hipMemcpyAsync(h->h_err, h->err, 2 * sizeof(int), hipMemcpyDeviceToHost, h->stream), "copy flag");
-    hip_check(hipMemcpyAsync(h->h_res, h->res, (h->dim + 2) * sizeof(double), hipMemcpyDeviceToHost, h->stream),
-              "copy residual");
+    hip_check(hipMemcpyAsync(h->h_stat, h->stat, (1 + (size_t)(h->dim + 2)) * sizeof(double), hipMemcpyDeviceToHost,
+                             h->stream), "copy flag and residual");
     hip_check(hipEventRecord(h->done_ev, h->stream), "hipEventRecord");
     h->pending = 1;
 }
 
 void release(ugks_t *h)
 {
-    if (h->h_err) (void)hipHostFree(h->h_err);
-    if (h->h_res) (void)hipHostFree(h->h_res);
+    if (h->h_stat) (void)hipHostFree(h->h_stat);
     if (h->done_ev) (void)hipEventDestroy(h->done_ev);
-    void *ptrs[] = {h->f[0], h->f[1], h->cgeo, h->fgeo, h->feq, h->u, h->w, h->bcp, h->W, h->q, h->gW, h->dW2,
-                    h->cell_dt, h->res, h->err, h->u1d, h->kidx, h->wallf, h->wallF, h->surf, h->ring, h->mom_part, h->rho_w,
+    void *ptrs[] = {h->f[0], h->f[1], h->cgeo, h->fgeo, h->feq, h->u, h->w, h->bcp, h->W, h->gW, h->dW2,
+                    h->cell_dt, h->stat, h->u1d, h->kidx, h->wallf, h->wallF, h->surf, h->ring, h->mom_part, h->rho_w,
                     h->mom_s, h->cconst, h->colour_cells, h->wall_cells, h->wall_index};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
@@ -705,13 +719,14 @@ extern "C" int ugks_create(const ugks_mesh_t *mesh, const ugks_vgrid_t *vgrid, c
         h->u = dev_alloc<double>(h, uT.size());
         h->w = dev_alloc<double>(h, nv);
         h->bcp = dev_alloc<double>(h, (size_t)std::max(1, h->nbc) * (D + 2));
-        h->W = dev_alloc<double>(h, nc * (D + 2));
-        h->q = dev_alloc<double>(h, nc * D);
+        h->W = dev_alloc<double>(h, nc * (2 * D + 2));  // W, and q behind it (read out together)
+        h->q = h->W + nc * (D + 2);
         h->gW = dev_alloc<double>(h, nc * (D + 2) * D);
         h->dW2 = dev_alloc<double>(h, nc * (D + 2));
         h->cell_dt = dev_alloc<double>(h, nc);
-        h->res = dev_alloc<double>(h, (D + 2) * (1 + (size_t)residual_groups((int)nc)));
-        h->err = dev_alloc<int>(h, 2);
+        h->stat = dev_alloc<double>(h, 1 + (D + 2) * (1 + (size_t)residual_groups((int)nc)));
+        h->err = reinterpret_cast<int *>(h->stat);
+        h->res = h->stat + 1;
         {
             std::vector<std::pair<int, int>> wf;  // (caller's face, stored face)
             for (int f = 0; f < h->nf; ++f)
@@ -897,14 +912,13 @@ extern "C" int ugks_step(ugks_t *h, int nsteps, double *residual_out)
             h->nstep++;
             h->stepped = 1;
         }
-        int err[2];
-        hip_check(hipMemcpyAsync(err, h->err, sizeof(err), hipMemcpyDeviceToHost, h->stream), "copy error flag");
-        if (residual_out && nsteps > 0) {
-            hip_check(launch_residual(h->P, h->res, h->stream), "residual launch");
-            hip_check(hipMemcpyAsync(residual_out, h->res, sizeof(double) * (h->dim + 2), hipMemcpyDeviceToHost, h->stream),
-                      "copy residual");
-        }
+        const bool want = residual_out && nsteps > 0;
+        if (want) hip_check(launch_residual(h->P, h->res, h->stream), "residual launch");
+        hip_check(hipMemcpyAsync(h->s_err, h->stat, sizeof(double) * (1 + (want ? (size_t)(h->dim + 2) : 0)),
+                                 hipMemcpyDeviceToHost, h->stream), "copy error flag and residual");
         hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+        const int err[2] = {h->s_err[0], h->s_err[1]};
+        if (want) std::copy(h->s_res, h->s_res + h->dim + 2, residual_out);
         if (h->profiling)
             for (int s = 0; s < nsteps; ++s) {
                 float a = 0.f, b = 0.f;
@@ -990,11 +1004,15 @@ extern "C" int ugks_macros(ugks_t *h, double *W_out, double *q_out)
 {
     if (!h) return UGKS_ERR_ARG;
     try {
-        const size_t nc = h->nc, NW = h->dim + 2, D = h->dim;
-        std::vector<double> W(W_out ? nc * NW : 0), q(q_out ? nc * D : 0);
-        if (W_out) hip_check(hipMemcpyAsync(W.data(), h->W, sizeof(double) * W.size(), hipMemcpyDeviceToHost, h->stream), "copy W");
-        if (q_out) hip_check(hipMemcpyAsync(q.data(), h->q, sizeof(double) * q.size(), hipMemcpyDeviceToHost, h->stream), "copy q");
+        const size_t nc = h->nc, NW = h->dim + 2, D = h->dim, n = nc * (NW + D);
+        // W and q in one copy: through the handle's pinned memory where they
+        // are small, else through a buffer of this call
+        std::unique_ptr<double[]> own;
+        if (!h->h_macro) own.reset(new double[n]);
+        double *buf = h->h_macro ? h->h_macro : own.get();
+        hip_check(hipMemcpyAsync(buf, h->W, sizeof(double) * n, hipMemcpyDeviceToHost, h->stream), "copy W and q");
         hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+        const double *W = buf, *q = buf + nc * NW;
         for (size_t i = 0; i < nc; ++i) {
             const size_t c = h->cell_of[i];
             if (W_out) std::copy(&W[i * NW], &W[i * NW] + NW, W_out + c * NW);
@@ -1449,9 +1467,8 @@ hipError_t batch_launch(ugks_t *const *hs, int n, int nsteps, const BatchItem *d
         h->stepped = 1;
         h->base_ok = 0;  // gather steps: the second buffer no longer holds the base
         h->last_push = 0;
-        e = hipMemcpyAsync(h->h_err, h->err, 2 * sizeof(int), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(h->h_res, h->res, (h->dim + 2) * sizeof(double), hipMemcpyDeviceToHost, h->stream);
+        e = hipMemcpyAsync(h->h_stat, h->stat, (1 + (size_t)(h->dim + 2)) * sizeof(double), hipMemcpyDeviceToHost,
+                           h->stream);
         if (e == hipSuccess) e = hipEventRecord(h->done_ev, h->stream);
         if (e == hipSuccess) h->pending = 1;
     }
