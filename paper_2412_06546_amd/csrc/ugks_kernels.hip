@@ -133,7 +133,7 @@ template <int D> __device__ __forceinline__ Prim<D> to_prim(const double *W)
 #pragma unroll
     for (int d = 0; d < D; ++d) {
         p.U[d] = W[1 + d] / p.rho;
-        ke += p.U[d] * p.U[d];
+        ke = fma(p.U[d], p.U[d], ke);  // (which product of a sum is fused may not be left to each kernel)
     }
     p.lam = N_DOF * p.rho / (4.0 * (W[D + 1] - 0.5 * p.rho * ke));
     return p;
