@@ -234,16 +234,16 @@ def json_safe(x):
 def sweep_kernels(run, mem):
     """The kernels one timed sweep launch consists of."""
     if run.get("sweep") == "push_unordered":
-        launches = "one launch of k_push_pf (k_push) over all cells in stored order"
+        launches = "one launch of k_push_brick (k_push_pf, k_push) over all cells in stored order"
     else:
-        launches = f"{run.get('n_colours')} colour launches of k_push_pf (k_push)"
+        launches = f"{run.get('n_colours')} colour launches of k_push_brick (k_push_pf, k_push)"
     if mem == "in-place" and run.get("sweep", "").startswith("push"):
         return (f"push sweep in place: k_push_wall, then per velocity chunk k_push_chunk_turn and {launches}, "
                 f"a last k_push_chunk_turn, k_push_final_inplace, timed together")
     if mem == "in-place":
         return "k_sweep_chunk (every chunk) + k_sweep_finish"
     if run.get("sweep", "").startswith("push"):
-        return f"push sweep: k_push_wall, {launches}, k_push_final_r (k_push_final), timed together"
+        return f"push sweep: k_push_wall, {launches}, k_push_final, timed together"
     return "k_sweep_pf (k_sweep)"
 
 

@@ -115,8 +115,9 @@ typedef struct {
 /* How the per-velocity sweep (the velocity loop of Algorithm 1) evaluates the
  * face fluxes.
  * UGKS_SWEEP_PUSH: every face flux once per velocity, by the face's upwind
- * cell with its own limited slope; the cells are coloured so that no two
- * cells of a colour are neighbours or share one, one launch per colour adds
+ * cell with its own limited slope; the cells (FP64 f in two buffers from
+ * 32,768 cells: bricks of 4 cells) are coloured so that no two of a colour
+ * are neighbours or share one, one launch per colour adds
  * each flux to the stage-1 values of both of its cells (the second f buffer
  * holds them; in the in-place mode a ring of one velocity chunk does, chunk
  * after chunk), and a final kernel forms W^{n+1}, q^{n+1} and stage 2.
@@ -310,9 +311,9 @@ int ugks_is_tensor_grid(const ugks_t *h);
 int ugks_sweep_kind(const ugks_t *h);
 /* The number of colour classes (launches per step, or per velocity chunk in
  * place) into which the push sweep splits the face-flux loop of Algorithm 1
- * (its velocity loop): cells of one class share no neighbour and are not neighbours; 1 for
- * the unordered push (one class of all cells), 0 when the handle gathers, -1
- * for a NULL handle. */
+ * (its velocity loop): cells (or bricks of cells) of one class share no
+ * neighbour and are not neighbours; 1 for the unordered push (one class of
+ * all cells), 0 when the handle gathers, -1 for a NULL handle. */
 int ugks_sweep_colours(const ugks_t *h);
 
 /* Timing of the step's kernels with HIP events on the handle's stream (the

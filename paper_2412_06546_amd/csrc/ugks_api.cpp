@@ -42,7 +42,7 @@ struct ugks {
     // face -> wall ordinal; whether the second buffer holds the stage-1 base
     // of the current f, and whether the last step was a push step (the wall
     // flux of that step is then already in wallF)
-    int push = 0, unordered = 0, base_ok = 0, last_push = 0;
+    int push = 0, unordered = 0, bricks = 0, base_ok = 0, last_push = 0;
     int *colour_cells = nullptr, *wall_cells = nullptr, *wall_index = nullptr;
     int n_wall_cells = 0;
     std::vector<int> colour_off;
@@ -444,39 +444,105 @@ void build_geometry(const StoredMesh &S, std::vector<CellGeo<D>> &cg, std::vecto
     }
 }
 
-// Colours of the push sweep: no two cells of a colour are neighbours or
-// share a neighbour (greedy distance-2 colouring in stored order); the
-// cells grouped by colour, stored order within a colour, and the offsets.
+// Colours of the push sweep over groups of cells (every cell its own group, or
+// bricks): no cell is written by two groups of a colour, where a group writes
+// its cells and their neighbours (greedy, groups in their order); the cells
+// grouped by colour, in the given order within a colour, and the offsets.
 template <int D>
-void push_colours(const std::vector<CellGeo<D>> &cg, std::vector<int> &cells, std::vector<int> &off)
+void push_colours(const std::vector<CellGeo<D>> &cg, const std::vector<int> &order, const std::vector<int> &group_of,
+                  int n_groups, std::vector<int> &cells, std::vector<int> &off)
 {
     const int nc = (int)cg.size();
-    std::vector<int> colour(nc, -1), stamp;
+    std::vector<int> colour(n_groups, -1), stamp;
     int ncol = 0;
-    for (int c = 0; c < nc; ++c) {
-        auto mark = [&](int d) {
-            if (d >= 0 && colour[d] >= 0) stamp[colour[d]] = c;
+    for (int a = 0; a < nc;) {
+        const int g = group_of[order[a]];
+        auto mark = [&](int c) {
+            if (c >= 0 && colour[group_of[c]] >= 0) stamp[colour[group_of[c]]] = g;
         };
-        for (int j = 0; j < cg[c].nf; ++j) {
-            const int n = cg[c].nb[j];
-            if (n < 0) continue;
-            mark(n);
-            for (int t = 0; t < cg[n].nf; ++t) mark(cg[n].nb[t]);
+        int b = a;
+        for (; b < nc && group_of[order[b]] == g; ++b) {
+            const int c = order[b];
+            for (int j = 0; j < cg[c].nf; ++j) {
+                const int n = cg[c].nb[j];
+                mark(n);
+                if (n < 0) continue;
+                for (int t = 0; t < cg[n].nf; ++t) mark(cg[n].nb[t]);
+            }
         }
         int k = 0;
-        while (k < ncol && stamp[k] == c) ++k;
+        while (k < ncol && stamp[k] == g) ++k;
         if (k == ncol) {
             ++ncol;
             stamp.push_back(-1);
         }
-        colour[c] = k;
+        colour[g] = k;
+        a = b;
     }
     off.assign(ncol + 1, 0);
-    for (int c = 0; c < nc; ++c) ++off[colour[c] + 1];
+    for (int c = 0; c < nc; ++c) ++off[colour[group_of[c]] + 1];
     for (int k = 0; k < ncol; ++k) off[k + 1] += off[k];
     cells.assign(nc, 0);
     std::vector<int> at(off.begin(), off.end() - 1);
-    for (int c = 0; c < nc; ++c) cells[at[colour[c]]++] = c;
+    for (int c : order) cells[at[colour[group_of[c]]]++] = c;
+}
+
+// The order of a push by bricks: from the first cell in stored order that
+// has no brick, a brick takes the free neighbour with the most faces to it
+// (the lowest stored cell among equals) until it has `size` cells, so that
+// groups of `size` consecutive entries are compact; cells of bricks that ran
+// out of free neighbours come last, each by itself, so that they shift no other
+// group.
+template <int D>
+std::vector<int> brick_order(const std::vector<CellGeo<D>> &cg, int size, std::vector<int> &brick_of, int &n_bricks)
+{
+    const int nc = (int)cg.size();
+    std::vector<int> order, rest, cand, links, cells;
+    order.reserve(nc);
+    brick_of.assign(nc, -1);
+    n_bricks = 0;
+    for (int first = 0; first < nc; ++first) {
+        if (brick_of[first] >= 0) continue;
+        const int brick = n_bricks++;
+        cells.clear();
+        cand.clear();
+        links.clear();
+        auto take = [&](int c) {
+            brick_of[c] = brick;
+            cells.push_back(c);
+            for (int j = 0; j < cg[c].nf; ++j) {
+                const int o = cg[c].nb[j];
+                if (o < 0 || brick_of[o] >= 0) continue;
+                size_t a = 0;
+                while (a < cand.size() && cand[a] != o) ++a;
+                if (a == cand.size()) {
+                    cand.push_back(o);
+                    links.push_back(0);
+                }
+                ++links[a];
+            }
+        };
+        take(first);
+        while ((int)cells.size() < size && !cand.empty()) {
+            size_t best = 0;
+            for (size_t a = 1; a < cand.size(); ++a)
+                if (links[a] > links[best] || (links[a] == links[best] && cand[a] < cand[best])) best = a;
+            const int c = cand[best];
+            cand[best] = cand.back();
+            links[best] = links.back();
+            cand.pop_back();
+            links.pop_back();
+            take(c);
+        }
+        std::vector<int> &to = (int)cells.size() == size ? order : rest;
+        to.insert(to.end(), cells.begin(), cells.end());
+    }
+    // a workgroup takes four of the remaining cells from anywhere in the list,
+    // so each is a group of its own: two cells of what was one brick may not
+    // meet in a launch of the coloured sweep, or the order of their adds is open
+    for (int c : rest) brick_of[c] = n_bricks++;
+    order.insert(order.end(), rest.begin(), rest.end());
+    return order;
 }
 
 template <int D> void create_d(ugks_t *h, const StoredMesh &S, const ugks_gas_t *gas)
@@ -486,12 +552,16 @@ template <int D> void create_d(ugks_t *h, const StoredMesh &S, const ugks_gas_t 
     build_geometry<D>(S, cg, fgv, gas->limiter_k);
     if (h->push) {
         std::vector<int> cells;
-        if (h->unordered) {  // one class: every cell, in stored order
-            cells.resize(cg.size());
-            for (size_t c = 0; c < cells.size(); ++c) cells[c] = (int)c;
-            h->colour_off = {0, (int)cg.size()};
+        const int nc = (int)cg.size();
+        int n_groups = nc;
+        std::vector<int> order(nc), group_of(nc);
+        for (int c = 0; c < nc; ++c) order[c] = group_of[c] = c;
+        if (h->bricks) order = brick_order<D>(cg, kBrickCells, group_of, n_groups);
+        if (h->unordered) {  // one class: every cell, in stored order (brick by brick)
+            cells = order;
+            h->colour_off = {0, nc};
         } else {
-            push_colours<D>(cg, cells, h->colour_off);
+            push_colours<D>(cg, order, group_of, n_groups, cells, h->colour_off);
         }
         h->colour_cells = dev_alloc<int>(h, cells.size());
         upload(h->colour_cells, cells.data(), sizeof(int) * cells.size(), h->stream);
@@ -538,6 +608,19 @@ bool uses_push(int dim, const ugks_gas_t *gas)
     if (asks_push(gas) || gas->mem_mode == UGKS_MEM_IN_PLACE) return true;
     return !(dim == 2 && gas->fstore == UGKS_F64);
 }
+// Whether a push handle with two buffers goes by bricks of cells (FP64 f:
+// with FP32 stage-1 sums the accumulator keeps its rounding per flux).  Two
+// workgroups have to fit a CU, and there have to be bricks for all of them in
+// a launch, as the velocities of a brick are not split over workgroups: from
+// 8,192 cells in one class, and 32,768 in the fifteen or so of the coloured
+// sweep; smaller meshes take a workgroup per cell and share of velocities.
+bool uses_bricks(int dim, const ugks_gas_t *gas, bool push, int nc, int ntab)
+{
+    const bool unordered = gas->sweep == UGKS_SWEEP_PUSH_UNORDERED;
+    return push && gas->fstore == UGKS_F64 && gas->mem_mode == UGKS_MEM_TWO_BUFFERS && nc >= (unordered ? 8192 : 32768) &&
+           brick_lds_bytes(dim, ntab) <= kBrickLds;
+}
+
 // the push sweep's running moment sums about U^n, per cell (in place)
 int shift_moments(int D) { return D == 2 ? 11 : 13; }
 
@@ -694,14 +777,15 @@ extern "C" int ugks_create(const ugks_mesh_t *mesh, const ugks_vgrid_t *vgrid, c
         StoredMesh S;
         relabel(mesh, S);
         h->cell_of = S.cell_of;
-        if (D == 2) create_d<2>(h, S, gas);
-        else create_d<3>(h, S, gas);
         int n1d[3] = {0, 0, 0};
         std::vector<double> axes;
         std::vector<int> kidx;
         h->tensor = detect_tensor(D, h->nv, vgrid->u, n1d, axes, kidx);
         // the per-workgroup Gaussian tables must fit in LDS next to the rest
         if (h->tensor && (size_t)(Dim<3>::MF + 1) * axes.size() * sizeof(double) > 48 * 1024) h->tensor = 0;
+        h->bricks = uses_bricks(D, gas, h->push, h->nc, h->tensor ? (int)axes.size() : 0) ? 1 : 0;
+        if (D == 2) create_d<2>(h, S, gas);
+        else create_d<3>(h, S, gas);
 
         const size_t nv = h->nv, nc = h->nc;
         h->perm = direction_order(D, h->nv, vgrid->u);
@@ -881,8 +965,8 @@ void sweep(ugks_t *h)
         hip_check(launch_sweep_inplace(h->P, h->f[0], h->n_wallf > 0, h->stream), "in-place sweep launch");
     } else if (h->push) {
         hip_check(launch_push_step(h->P, h->f[h->cur], h->f[1 - h->cur], !h->base_ok, h->colour_cells,
-                                   h->colour_off.data(), (int)h->colour_off.size() - 1, h->wall_cells, h->n_wall_cells,
-                                   h->stream),
+                                   h->colour_off.data(), (int)h->colour_off.size() - 1, h->bricks != 0,
+                                   h->wall_cells, h->n_wall_cells, h->stream),
                   "push sweep launch");
         h->base_ok = 1;
         h->last_push = 1;

@@ -38,6 +38,13 @@ template <int D> struct alignas(16) CellGeo {
     double nb_inv_vol[MF];  // 1 / |Omega_n| of the neighbour across each slot (0 on a boundary)
 };
 
+// Cells of a brick of the push sweep (FP64 f): the cell lists are ordered so
+// that groups of this many consecutive entries are compact.  The LDS of a
+// brick's workgroup (tables and sums), and what of it leaves room for two
+// workgroups a CU.
+constexpr int kBrickCells = 4, kBrickThreads = 768;
+constexpr size_t kBrickLds = 80 * 1024;
+
 template <int D> struct alignas(16) FaceGeo {
     int l, r, bc, bcid;
     double n[D];   // unit normal, left -> right
@@ -59,12 +66,15 @@ template <int D> struct alignas(16) FaceGeo {
 // c0, c1 free transport over the step, k0 = dt times the prefactor of the
 // Maxwellian that the incoming particles come from (a ghost, or the wall's
 // with unit density), all other coefficients zero.
-template <int D> struct alignas(16) FaceEq {
+template <int D> struct FaceEqB {};
+template <> struct FaceEqB<2> {
+    double bh, d0, d1[2];
+};
+template <int D> struct alignas(16) FaceEq : FaceEqB<D> {  // b's part in 2D only: the records share a 16 KB scalar cache
     static constexpr int NK2 = D * (D + 1) / 2;
     double U[D], lam;
     double c0, c1;
     double k0, k1[D], k2[NK2], k3[D];  // k2: c_a c_b, a <= b, row by row
-    double bh, d0, d1[D];              // 2D only (b); zero in 3D
 };
 
 // A cell's constants at t^n for the streaming kernels of the push sweep in
@@ -154,6 +164,7 @@ hipError_t launch_batch_residual(const BatchItem *items, int n, int dim, hipStre
 // workgroups of the per-cell sweep grid for nc cells (a multiple of the XCD span)
 int sweep_grid(int nc);
 
+size_t brick_lds_bytes(int dim, int ntab);
 hipError_t launch_cfl(const Params &p, double *cell_dt, hipStream_t s);
 hipError_t launch_init(const Params &p, const double *prim0, void *f, hipStream_t s);
 hipError_t launch_moments(const Params &p, const void *f, hipStream_t s);
@@ -163,9 +174,10 @@ hipError_t launch_sweep(const Params &p, const void *f_in, void *f_out, hipStrea
 // first when need_base, then the wall cells (wall densities into rho_w and
 // the step's wall flux), then one launch per colour over cells[coff[c] ..
 // coff[c+1]) (coff: host array of ncol + 1 offsets into the device list
-// cells), then stage 2 into f and the next base into acc
+// cells; bricks: in brick order, brick kernels), then stage 2
+// into f and the next base into acc
 hipError_t launch_push_step(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff,
-                            int ncol, const int *wall_cells, int n_wall_cells, hipStream_t s);
+                            int ncol, bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s);
 // the push sweep with one f buffer (FP64 or FP32 f): the wall cells, then per
 // velocity chunk the base into the ring, one launch per colour, the stage-1
 // values back into f; then W^{n+1}, q^{n+1} and stage 2 in place

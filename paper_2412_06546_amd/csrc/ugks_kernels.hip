@@ -14,9 +14,9 @@
 //                through, the interface flux of Eq. fullSolution integrated
 //                over the step, added with atomic adds into the stage-1 sums
 //                (Eq. microS1) of both of the face's cells: k_push_wall (wall
-//                densities), k_push_pf / k_push (per colour class of cells,
-//                or one launch of all cells), then k_push_final_r /
-//                k_push_final (W^{n+1}, q^{n+1}, stage 2 of Eq. microS2);
+//                densities), k_push_brick / k_push_pf / k_push (per colour class
+//                of cells, or one launch of all cells), then k_push_final
+//                (W^{n+1}, q^{n+1}, stage 2 of Eq. microS2);
 //   gather sweep k_sweep    per cell, one workgroup owning the cell's whole
 //                velocity slab: for every velocity the limited slope of f is
 //                rebuilt in registers (own cell, and upwind neighbours when
@@ -751,7 +751,7 @@ __device__ __forceinline__ void face_eq(const Params p, int f)
         e.c0 = p.dt;
         e.c1 = -0.5 * p.dt * p.dt;
         e.k0 = p.dt * rho * pow_lam_pi<D>(lam);
-        e.bh = Dim<D>::M / (2.0 * lam);
+        if constexpr (Dim<D>::M > 0) e.bh = Dim<D>::M / (2.0 * lam);
         return;
     }
     // reconstructed states on both sides
@@ -1806,6 +1806,121 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
     }
 }
 
+// The push sweep over bricks of kBrickCells cells (FP64 f): a workgroup
+// carries its velocities through one cell of its brick after the other, keeps
+// the stage-1 sums of the brick in LDS (a column per thread) and adds a flux
+// to them where the neighbour belongs to the brick.  The push is bound by its
+// atomic adds, which are performed beyond the L2 (without them k_push_pf takes
+// 6.5 ms of 12): a compact brick of 4 cells leaves 3 a cell and velocity
+// instead of 4.  107,118 cells x 4,548: all cells in one launch 11.97 -> 9.6
+// ms, 15 colours 14.2 -> 12.05.  Bricks of 2, 3 and 8 measured 11.1, 10.6 and
+// 18.0 against 10.2 (before whole bricks were put first in the list), and
+// workgroups of 256, 512 and 1,024 threads 13.4, 10.3 and 10.3: 768 threads at
+// two workgroups a CU keep 24 wavefronts on few enough records for the scalar
+// cache.
+template <int D, bool TENSOR>
+__global__ __launch_bounds__(kBrickThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_push_brick(
+    Params p, const double *__restrict__ fin, double *__restrict__ acc, const int *__restrict__ cells, int ncell)
+{
+    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NT = MF + 1, B = kBrickCells, BS = kBrickThreads;
+    extern __shared__ double smem[];
+    __shared__ double sums[B][NC][BS];
+    const int b = xcd_cell(blockIdx.x) * B;
+    if (b >= ncell) return;
+    const int nb = min(B, ncell - b), tid = threadIdx.x;
+    const CellGeo<D> *cg = static_cast<const CellGeo<D> *>(p.cgeo);
+    const FaceGeo<D> *fg = static_cast<const FaceGeo<D> *>(p.fgeo);
+    const FaceEq<D> *fe = static_cast<const FaceEq<D> *>(p.feq);
+    const int nv = p.nv, ntab = TENSOR ? p.ntab : 0, nt = NT * ntab;
+    int cell[B];
+#pragma unroll
+    for (int c = 0; c < B; ++c) cell[c] = c < nb ? cells[b + c] : -2;
+    if constexpr (TENSOR)
+        for (int c = 0; c < nb; ++c)
+            fill_tables<D, BS>(p, cg[cells[b + c]], to_prim<D>(p.W + (size_t)cells[b + c] * (D + 2)), smem + c * nt);
+    __syncthreads();
+    double pv0[NC], pvn[MF][NC];
+    if (tid < nv) load_stencil<D, double>(cg[cell[0]], cell[0], fin, nv, tid, pv0, pvn);
+    for (int k = tid; k < nv; k += BS) {
+#pragma unroll
+        for (int c = 0; c < B; ++c)
+#pragma unroll
+            for (int m = 0; m < NC; ++m) sums[c][m][tid] = 0.0;
+        double u[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) u[d] = p.u[d * nv + k];
+        const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
+#pragma unroll 1
+        for (int c = 0; c < nb; ++c) {
+            const int i = cells[b + c];
+            const CellGeo<D> &gi = cg[i];
+            const Gauss<D, TENSOR> gauss{smem + c * nt, ntab};
+            const int nf = gi.nf;
+            double v0[NC], vn[MF][NC];
+#pragma unroll
+            for (int m = 0; m < NC; ++m) {
+                v0[m] = pv0[m];
+#pragma unroll
+                for (int j = 0; j < MF; ++j) vn[j][m] = pvn[j][m];
+            }
+            {
+                const int cn = c + 1 < nb ? cells[b + c + 1] : cell[0], kk = c + 1 < nb ? k : k + BS;
+                if (kk < nv) load_stencil<D, double>(cg[cn], cn, fin, nv, kk, pv0, pvn);
+            }
+            double fi[NC], gri[NC][D], out[NC], ug[NC];
+            slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
+            along<D>(u, gri, ug);
+#pragma unroll
+            for (int m = 0; m < NC; ++m) out[m] = 0.0;
+#pragma unroll 1
+            for (int j = 0; j < nf; ++j) {
+                const int f = gi.face[j];
+                const FaceGeo<D> &F = fg[f];
+                const FaceEq<D> &e = fe[f];
+                double un = 0.0, I[NC];
+#pragma unroll
+                for (int d = 0; d < D; ++d) un = fma(u[d], F.n[d], un);
+                const double uo = gi.side[j] ? -un : un;  // along this cell's outward normal
+                if (F.bc == 0) {
+                    if (!(uo > 0.0)) continue;  // the neighbour is upwind: it adds this flux
+                    const int n = gi.nb[j];
+                    int to = -1;
+#pragma unroll
+                    for (int q = 0; q < B; ++q) to = n == cell[q] ? q : to;
+                    interface_integral<D>(e, u, gauss(j, kx, u, e.lam, e.U), fi, gri, gi.dvec[j], ug, I);
+                    const double sa = F.area * uo, vn_inv = gi.nb_inv_vol[j];
+#pragma unroll
+                    for (int m = 0; m < NC; ++m) {
+                        const double fl = sa * I[m];
+                        out[m] += fl;
+                        if (to >= 0) unsafeAtomicAdd(&sums[to][m][tid], fl * vn_inv);
+                        else unsafeAtomicAdd(acc + (size_t)n * NC * nv + (size_t)m * nv + k, fl * vn_inv);
+                    }
+                } else {
+                    if (un > 0.0) {
+                        boundary_outgoing<D>(e, fi, gri, gi.dvec[j], ug, I);
+                    } else {
+                        // incoming from the wall (density rho_w) or the ghost Maxwellian
+                        I[0] = (F.bc == 3 ? p.rho_w[(size_t)i * MF + j] : 1.0) * e.k0 * gauss(j, kx, u, e.lam, e.U);
+                        if constexpr (NC > 1) I[NC - 1] = e.bh * I[0];
+                    }
+                    const double sa = F.area * un;  // a boundary cell is the face's left cell
+#pragma unroll
+                    for (int m = 0; m < NC; ++m) out[m] += sa * I[m];
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < NC; ++m) unsafeAtomicAdd(&sums[c][m][tid], -out[m] * gi.inv_vol);
+        }
+#pragma unroll
+        for (int c = 0; c < B; ++c)
+            if (c < nb)
+#pragma unroll
+                for (int m = 0; m < NC; ++m)
+                    unsafeAtomicAdd(acc + ((size_t)cell[c] * NC + m) * nv + k, sums[c][m][tid]);
+    }
+}
+
 // The wall cells of a step (before the colours): wall densities per face slot
 // into rho_w [cell][MF] and the wall flux of the step per wall face.
 template <int D, typename FT, int BS, bool TENSOR>
@@ -1938,7 +2053,7 @@ __global__ __launch_bounds__(BS) void k_wall_flux(Params p, const FT *__restrict
                 c2 += cd * cd;
             }
             I[0] = e.k0 * exp(-e.lam * c2);
-            I[1] = NC > 1 ? e.bh * I[0] : 0.0;
+            if constexpr (NC > 1) I[1] = e.bh * I[0];
             off = NW;
         }
         const double a = wk * un;
@@ -2972,9 +3087,15 @@ void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_
     else launch_final_form<D, FT, TENSOR, 1024, 8>(p, f, acc, s);  // up to 16,384 velocities
 }
 
+size_t brick_lds_bytes(int dim, int ntab)
+{
+    const size_t mf = dim == 2 ? Dim<2>::MF : Dim<3>::MF, nc = dim == 2 ? Dim<2>::NC : Dim<3>::NC;
+    return sizeof(double) * kBrickCells * ((mf + 1) * (size_t)ntab + nc * kBrickThreads);
+}
+
 template <int D, typename FT, bool TENSOR>
 hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int *cells, const int *coff, int ncol,
-                  const int *wall_cells, int n_wall_cells, hipStream_t s)
+                  bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
 {
     constexpr int MF = Dim<D>::MF, NW = D + 2, BS = 256;
     using AT = typename AccOf<FT>::T;
@@ -2990,6 +3111,13 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
     for (int c = 0; c < ncol; ++c) {
         const int n = coff[c + 1] - coff[c];
         if (n <= 0) continue;
+        if constexpr (sizeof(FT) == 8) {
+            if (bricks) {
+                hipLaunchKernelGGL((k_push_brick<D, TENSOR>), dim3(sweep_grid((n + kBrickCells - 1) / kBrickCells)),
+                                   dim3(kBrickThreads), tab * kBrickCells, s, p, fin, acc, cells + coff[c], n);
+                continue;
+            }
+        }
         const unsigned g = (unsigned)sweep_grid(n);
         const int ks = push_ksplit(n, p.nv, BS);
         const dim3 grid(g, (unsigned)((p.nv + ks - 1) / ks));
@@ -3006,10 +3134,10 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
 
 template <int D, typename FT>
 hipError_t push_d(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff, int ncol,
-                  const int *wc, int nwc, hipStream_t s)
+                  bool bricks, const int *wc, int nwc, hipStream_t s)
 {
-    return p.ntab > 0 ? push_t<D, FT, true>(p, f, acc, need_base, cells, coff, ncol, wc, nwc, s)
-                      : push_t<D, FT, false>(p, f, acc, need_base, cells, coff, ncol, wc, nwc, s);
+    return p.ntab > 0 ? push_t<D, FT, true>(p, f, acc, need_base, cells, coff, ncol, bricks, wc, nwc, s)
+                      : push_t<D, FT, false>(p, f, acc, need_base, cells, coff, ncol, bricks, wc, nwc, s);
 }
 
 template <int D, typename FT, bool TENSOR>
@@ -3079,16 +3207,16 @@ hipError_t launch_push_inplace(const Params &p, void *f, const int *cells, const
 }
 
 hipError_t launch_push_step(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff,
-                            int ncol, const int *wall_cells, int n_wall_cells, hipStream_t s)
+                            int ncol, bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
 {
     // bfloat16 f: acc holds FP32 stage-1 sums
     if (p.dim == 2)
-        return p.fstore == 2 ? push_d<2, bf16s>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s)
-               : p.fstore    ? push_d<2, float>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s)
-                             : push_d<2, double>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s);
-    return p.fstore == 2 ? push_d<3, bf16s>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s)
-           : p.fstore    ? push_d<3, float>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s)
-                         : push_d<3, double>(p, f, acc, need_base, cells, coff, ncol, wall_cells, n_wall_cells, s);
+        return p.fstore == 2 ? push_d<2, bf16s>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s)
+               : p.fstore    ? push_d<2, float>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s)
+                             : push_d<2, double>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s);
+    return p.fstore == 2 ? push_d<3, bf16s>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s)
+           : p.fstore    ? push_d<3, float>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s)
+                         : push_d<3, double>(p, f, acc, need_base, cells, coff, ncol, bricks, wall_cells, n_wall_cells, s);
 }
 
 // Surface quantities of Section 2.5 from the wall flux of the last step (per
