@@ -596,8 +596,9 @@ int nchunk_of(int chunk, int nv) { return (nv + chunk - 1) / chunk; }
 // whether a handle sweeps by pushing each face flux once (else gathering).
 // Automatic choice: push, except for 2D with FP64 f in two buffers, where
 // gathering is faster on MI355X (2D hypersonic cylinder, 20,000 cells x
-// 3,600 velocities: 3.2 against 4.2 ms per step; FP32 f 2.7 push against 2.9
-// gather; the 3D lifting body 178 push against 295 ms gather in FP64).
+// 3,600 velocities: 2.6 against 3.8 ms per step; FP32 f 2.4 push against 3.2
+// gather; the 3D lifting body on 107,118 cells 15.6 push against 25.3 gather
+// in FP64).
 // BF16 f pushes only when asked: its accumulator (the second buffer, or the
 // ring in place) holds FP32 stage-1 sums, 2 more bytes per value.
 bool asks_push(const ugks_gas_t *gas) { return gas->sweep == UGKS_SWEEP_PUSH || gas->sweep == UGKS_SWEEP_PUSH_UNORDERED; }
@@ -613,7 +614,9 @@ bool uses_push(int dim, const ugks_gas_t *gas)
 // workgroups have to fit a CU, and there have to be bricks for all of them in
 // a launch, as the velocities of a brick are not split over workgroups: from
 // 8,192 cells in one class, and 32,768 in the fifteen or so of the coloured
-// sweep; smaller meshes take a workgroup per cell and share of velocities.
+// sweep; smaller meshes take a workgroup per cell and share of velocities
+// (9,261 cells x 2,145 in one launch: 421 us by bricks, 427 by cells; a class
+// of 32,768 cells in fifteen colours is 546 bricks, two for every CU).
 bool uses_bricks(int dim, const ugks_gas_t *gas, bool push, int nc, int ntab)
 {
     const bool unordered = gas->sweep == UGKS_SWEEP_PUSH_UNORDERED;
