@@ -922,6 +922,9 @@ __device__ __forceinline__ int xcd_cell(int b)
     return ((t / UGKS_XCD_RUN) * UGKS_XCDS + b % UGKS_XCDS) * UGKS_XCD_RUN + t % UGKS_XCD_RUN;
 }
 
+// The workgroup's index where the workgroups of a launch go in rows (cell_grid)
+__device__ __forceinline__ int row_block() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+
 // Per-cell constants of a step (uniform in the workgroup): W^n, the
 // primitive state, tau^n, q^n and the coefficients of f+^n and of the source.
 template <int D> struct CellStep {
@@ -2281,6 +2284,16 @@ int sweep_grid(int nc)
     return ((nc + span - 1) / span) * span;
 }
 
+// The same as a grid of workgroups of bs threads.  A dimension of a launch
+// takes fewer than 2^32 work-items, which 16,000,000 workgroups of 256 threads
+// keep and wider ones do not: those go in rows (row_block).
+inline dim3 cell_grid(int nc, int bs)
+{
+    constexpr unsigned span = UGKS_XCDS * UGKS_XCD_RUN;
+    const unsigned n = (unsigned)sweep_grid(nc), row = 0xffffffffu / (unsigned)bs / span * span;
+    return n <= row ? dim3(n) : dim3(row, (n + row - 1) / row);
+}
+
 template <int D, typename FT, int BS, bool TENSOR>
 void sweep_launch(const Params &p, const void *fi, void *fo, hipStream_t s)
 {
@@ -2640,7 +2653,7 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
     using AT = typename AccOf<FT>::T;
     constexpr int NC = Dim<D>::NC, NW = D + 2;
     extern __shared__ double smem[];
-    const int i = xcd_cell(blockIdx.x);
+    const int i = xcd_cell(row_block());
     if (i >= p.nc) return;
     const int nv = p.nv, tid = threadIdx.x;
     const bool aligned = nv % 2 == 0;
@@ -2731,7 +2744,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
     using AT = typename AccOf<FT>::T;
     constexpr int NC = Dim<D>::NC, NW = D + 2, N = Shift<D>::N;
     extern __shared__ double smem[];
-    const int i = xcd_cell(blockIdx.x);
+    const int i = xcd_cell(row_block());
     if (i >= p.nc) return;
     const int tid = threadIdx.x, nv = p.nv;
     const bool aligned = nv % 2 == 0;
@@ -3063,7 +3076,7 @@ template <int D, typename FT, bool TENSOR, int BS>
 void launch_base_form(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
     const size_t lds = sizeof(double) * ((TENSOR ? 2 * (size_t)p.ntab : 0) + (BS / 64) * (D + 2));
-    hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, BS>), dim3(sweep_grid(p.nc)), dim3(BS), lds, s, p, f, acc);
+    hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, BS>), cell_grid(p.nc, BS), dim3(BS), lds, s, p, f, acc);
 }
 template <int D, typename FT, bool TENSOR>
 void launch_base(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
@@ -3076,7 +3089,7 @@ template <int D, typename FT, bool TENSOR, int BS, int NP>
 void launch_final_form(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
     const size_t lds = sizeof(double) * ((TENSOR ? 3 * (size_t)p.ntab : 0) + (BS / 64) * Shift<D>::N + 4 + 2 * D);
-    hipLaunchKernelGGL((k_push_final<D, FT, TENSOR, BS, NP>), dim3(sweep_grid(p.nc)), dim3(BS), lds, s, p, f, acc);
+    hipLaunchKernelGGL((k_push_final<D, FT, TENSOR, BS, NP>), cell_grid(p.nc, BS), dim3(BS), lds, s, p, f, acc);
 }
 template <int D, typename FT, bool TENSOR>
 void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
