@@ -135,7 +135,7 @@ template <int D> __device__ __forceinline__ Prim<D> to_prim(const double *W)
         p.U[d] = W[1 + d] / p.rho;
         ke = fma(p.U[d], p.U[d], ke);  // (which product of a sum is fused may not be left to each kernel)
     }
-    p.lam = N_DOF * p.rho / (4.0 * (W[D + 1] - 0.5 * p.rho * ke));
+    p.lam = N_DOF * p.rho / (4.0 * fma(-0.5 * p.rho, ke, W[D + 1]));
     return p;
 }
 
@@ -297,6 +297,8 @@ __device__ __forceinline__ void limited_slope(const CellGeo<D> &g, int c, const 
 // Maxwellian value H there (Section 2.2):
 // H+ = shk (c.q)(2 lam c^2 - 2 - D) H, B = M/(2 lam) H,
 // B+ = shk (c.q)(2 lam c^2 - D) B, with shk = 4 (1 - Pr) lam^2 / (5 rho).
+// Every multiply-add is written out: the push sweep's base and final kernels
+// have to form the same bits, which may not hang on what the compiler fuses.
 template <int D>
 __device__ __forceinline__ void shakhov_at(const double (&c)[D], double c2, double lam, double shk, const double (&q)[D],
                                            double bh, double H, double &fh, double &fb)
@@ -305,11 +307,11 @@ __device__ __forceinline__ void shakhov_at(const double (&c)[D], double c2, doub
     double cq = 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) cq = fma(c[d], q[d], cq);
-    const double s = shk * cq, l2 = 2.0 * lam * c2;
-    fh = fma(s * (l2 - 2.0 - D), H, H);
+    const double s = shk * cq, l = 2.0 * lam;
+    fh = fma(s * fma(l, c2, -(2.0 + D)), H, H);
     if constexpr (M > 0) {
         const double B = bh * H;  // bh = M / (2 lam)
-        fb = fma(s * (l2 - D), B, B);
+        fb = fma(s * fma(l, c2, -(double)D), B, B);
     } else {
         fb = 0.0;
     }
