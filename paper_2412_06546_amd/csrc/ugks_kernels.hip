@@ -190,33 +190,40 @@ __device__ __forceinline__ double rcp_nr(double x)
 // branch.  Loads take a uniform base and a 32-bit byte offset (a cell's slab
 // is far below 4 GiB).  The sweep loads the next velocity's stencil while it
 // works on the current one; limited_slope = load_stencil + slope_from.
-template <typename FT>
-__device__ __forceinline__ double load_at(const FT *__restrict__ base, unsigned idx)
+template <typename FT> __device__ __forceinline__ FT load_at(const FT *__restrict__ base, unsigned idx)
 {
-    return to_f64(*reinterpret_cast<const FT *>(reinterpret_cast<const char *>(base) + idx * (unsigned)sizeof(FT)));
+    return *reinterpret_cast<const FT *>(reinterpret_cast<const char *>(base) + idx * (unsigned)sizeof(FT));
 }
+
+// The values stay in their storage type until the slope uses them: widened on
+// arrival, a prefetched FP32 stencil takes twice the registers, and where that
+// made the gather sweep spill, the reload inside its velocity loop waited for
+// the prefetch behind it as well (20,000 cells x 3,600 in 2D with FP32 f: 3.20
+// ms a step, 2.12 without).
+template <int D, typename FT> struct Stencil {
+    FT v0[Dim<D>::NC], vn[Dim<D>::MF][Dim<D>::NC];
+};
 
 template <int D, typename FT>
 __device__ __forceinline__ void load_stencil(const CellGeo<D> &g, int c, const FT *__restrict__ f, int nv, int k,
-                                             double (&v0)[Dim<D>::NC], double (&vn)[Dim<D>::MF][Dim<D>::NC])
+                                             Stencil<D, FT> &s)
 {
     constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF;
     const FT *fcell = f + (size_t)c * NC * nv;
 #pragma unroll
-    for (int m = 0; m < NC; ++m) v0[m] = load_at(fcell, (unsigned)(m * nv + k));
+    for (int m = 0; m < NC; ++m) s.v0[m] = load_at(fcell, (unsigned)(m * nv + k));
 #pragma unroll
     for (int j = 0; j < MF; ++j) {
         const int n = g.nb[j];
         const FT *fnb = f + (size_t)(n < 0 ? c : n) * NC * nv;
 #pragma unroll
-        for (int m = 0; m < NC; ++m) vn[j][m] = load_at(fnb, (unsigned)(m * nv + k));
+        for (int m = 0; m < NC; ++m) s.vn[j][m] = load_at(fnb, (unsigned)(m * nv + k));
     }
 }
 
-template <int D>
-__device__ __forceinline__ void slope_from(const CellGeo<D> &g, int limiter, const double (&v0)[Dim<D>::NC],
-                                           const double (&vn)[Dim<D>::MF][Dim<D>::NC], double (&fc)[Dim<D>::NC],
-                                           double (&gr)[Dim<D>::NC][D])
+template <int D, typename FT>
+__device__ __forceinline__ void slope_from(const CellGeo<D> &g, int limiter, const Stencil<D, FT> &st,
+                                           double (&fc)[Dim<D>::NC], double (&gr)[Dim<D>::NC][D])
 {
     constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF;
     // extremes of the differences f_j - f_i (0 for the cell itself): equal to
@@ -224,7 +231,7 @@ __device__ __forceinline__ void slope_from(const CellGeo<D> &g, int limiter, con
     double up[NC], dn[NC];
 #pragma unroll
     for (int m = 0; m < NC; ++m) {
-        fc[m] = v0[m];
+        fc[m] = to_f64(st.v0[m]);
         up[m] = dn[m] = 0.0;
 #pragma unroll
         for (int d = 0; d < D; ++d) gr[m][d] = 0.0;
@@ -236,7 +243,7 @@ __device__ __forceinline__ void slope_from(const CellGeo<D> &g, int limiter, con
         if (j > D && j >= nf) break;
 #pragma unroll
         for (int m = 0; m < NC; ++m) {
-            const double df = vn[j][m] - fc[m];
+            const double df = to_f64(st.vn[j][m]) - fc[m];
 #pragma unroll
             for (int d = 0; d < D; ++d) gr[m][d] = fma(g.lsq[j][d], df, gr[m][d]);
             up[m] = fmax(up[m], df);
@@ -288,9 +295,9 @@ template <int D, typename FT>
 __device__ __forceinline__ void limited_slope(const CellGeo<D> &g, int c, const FT *__restrict__ f, int nv, int k,
                                               int limiter, double (&fc)[Dim<D>::NC], double (&gr)[Dim<D>::NC][D])
 {
-    double v0[Dim<D>::NC], vn[Dim<D>::MF][Dim<D>::NC];
-    load_stencil<D, FT>(g, c, f, nv, k, v0, vn);
-    slope_from<D>(g, limiter, v0, vn, fc, gr);
+    Stencil<D, FT> st;
+    load_stencil<D, FT>(g, c, f, nv, k, st);
+    slope_from<D, FT>(g, limiter, st, fc, gr);
 }
 
 // Shakhov equilibrium f+ = H + H+ (and B + B+) at u, given the reduced
@@ -1284,18 +1291,13 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
     double mom[NW];
 #pragma unroll
     for (int m = 0; m < NW; ++m) mom[m] = 0.0;
-    double pv0[NC], pvn[MF][NC];
-    if (PF && s1_off + tid < k_end) load_stencil<D, FT>(gi, i, fin, nv, s1_off + tid, pv0, pvn);
+    Stencil<D, FT> next;
+    if (PF && s1_off + tid < k_end) load_stencil<D, FT>(gi, i, fin, nv, s1_off + tid, next);
     for (int k = s1_off + tid; k < k_end; k += BS) {
-        double v0[NC], vn[MF][NC];
+        Stencil<D, FT> own;
         if constexpr (PF) {
-#pragma unroll
-            for (int m = 0; m < NC; ++m) {
-                v0[m] = pv0[m];
-#pragma unroll
-                for (int j = 0; j < MF; ++j) vn[j][m] = pvn[j][m];
-            }
-            if (k + BS < k_end) load_stencil<D, FT>(gi, i, fin, nv, k + BS, pv0, pvn);
+            own = next;
+            if (k + BS < k_end) load_stencil<D, FT>(gi, i, fin, nv, k + BS, next);
         }
         double u[D], u2 = 0.0;
 #pragma unroll
@@ -1305,7 +1307,7 @@ __device__ __forceinline__ void sweep_cell(const Params p, int i, const FT *__re
         }
         const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
         double fi[NC], gri[NC][D];
-        if constexpr (PF) slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
+        if constexpr (PF) slope_from<D, FT>(gi, p.limiter, own, fi, gri);
         else limited_slope<D, FT>(gi, i, fin, nv, k, p.limiter, fi, gri);
         double out[NC], ugi[NC];
         along<D>(u, gri, ugi);
@@ -1732,20 +1734,15 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
     // cell and component, starting at k0 (the whole set, or one chunk)
     const int kend = k0 + kn;
     const size_t base = (size_t)i * NC * accv;
-    double pv0[NC], pvn[MF][NC];
-    if (PF && k0 + tid < kend) load_stencil<D, FT>(gi, i, fin, nv, k0 + tid, pv0, pvn);
+    Stencil<D, FT> next;
+    if (PF && k0 + tid < kend) load_stencil<D, FT>(gi, i, fin, nv, k0 + tid, next);
     for (int k = k0 + tid; k < kend; k += BS) {
-        double v0[NC], vn[MF][NC];
+        Stencil<D, FT> own;
         if constexpr (PF) {
-#pragma unroll
-            for (int m = 0; m < NC; ++m) {
-                v0[m] = pv0[m];
-#pragma unroll
-                for (int j = 0; j < MF; ++j) vn[j][m] = pvn[j][m];
-            }
-            if (k + BS < kend) load_stencil<D, FT>(gi, i, fin, nv, k + BS, pv0, pvn);
+            own = next;
+            if (k + BS < kend) load_stencil<D, FT>(gi, i, fin, nv, k + BS, next);
         } else {
-            load_stencil<D, FT>(gi, i, fin, nv, k, v0, vn);
+            load_stencil<D, FT>(gi, i, fin, nv, k, own);
         }
         double u[D], u2 = 0.0;
 #pragma unroll
@@ -1755,7 +1752,7 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
         }
         const unsigned kx = TENSOR ? (unsigned)p.kidx[k] : 0u;
         double fi[NC], gri[NC][D];
-        slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
+        slope_from<D, FT>(gi, p.limiter, own, fi, gri);
         double out[NC], ug[NC];
         along<D>(u, gri, ug);
 #pragma unroll
@@ -1844,8 +1841,8 @@ __global__ __launch_bounds__(kBrickThreads) __attribute__((amdgpu_waves_per_eu(6
         for (int c = 0; c < nb; ++c)
             fill_tables<D, BS>(p, cg[cells[b + c]], to_prim<D>(p.W + (size_t)cells[b + c] * (D + 2)), smem + c * nt);
     __syncthreads();
-    double pv0[NC], pvn[MF][NC];
-    if (tid < nv) load_stencil<D, double>(cg[cell[0]], cell[0], fin, nv, tid, pv0, pvn);
+    Stencil<D, double> next;
+    if (tid < nv) load_stencil<D, double>(cg[cell[0]], cell[0], fin, nv, tid, next);
     for (int k = tid; k < nv; k += BS) {
 #pragma unroll
         for (int c = 0; c < B; ++c)
@@ -1861,19 +1858,13 @@ __global__ __launch_bounds__(kBrickThreads) __attribute__((amdgpu_waves_per_eu(6
             const CellGeo<D> &gi = cg[i];
             const Gauss<D, TENSOR> gauss{smem + c * nt, ntab};
             const int nf = gi.nf;
-            double v0[NC], vn[MF][NC];
-#pragma unroll
-            for (int m = 0; m < NC; ++m) {
-                v0[m] = pv0[m];
-#pragma unroll
-                for (int j = 0; j < MF; ++j) vn[j][m] = pvn[j][m];
-            }
+            const Stencil<D, double> own = next;
             {
                 const int cn = c + 1 < nb ? cells[b + c + 1] : cell[0], kk = c + 1 < nb ? k : k + BS;
-                if (kk < nv) load_stencil<D, double>(cg[cn], cn, fin, nv, kk, pv0, pvn);
+                if (kk < nv) load_stencil<D, double>(cg[cn], cn, fin, nv, kk, next);
             }
             double fi[NC], gri[NC][D], out[NC], ug[NC];
-            slope_from<D>(gi, p.limiter, v0, vn, fi, gri);
+            slope_from<D, double>(gi, p.limiter, own, fi, gri);
             along<D>(u, gri, ug);
 #pragma unroll
             for (int m = 0; m < NC; ++m) out[m] = 0.0;
