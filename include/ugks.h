@@ -115,9 +115,9 @@ typedef struct {
 /* How the per-velocity sweep (the velocity loop of Algorithm 1) evaluates the
  * face fluxes.
  * UGKS_SWEEP_PUSH: every face flux once per velocity, by the face's upwind
- * cell with its own limited slope; the cells (FP64 f in two buffers from
- * 32,768 cells: bricks of 4 cells) are coloured so that no two of a colour
- * are neighbours or share one, one launch per colour adds
+ * cell with its own limited slope; the cells (FP64 f in two buffers, where
+ * cells and velocities are many enough: bricks of 4 cells) are coloured so that
+ * no two of a colour are neighbours or share one, one launch per colour adds
  * each flux to the stage-1 values of both of its cells (the second f buffer
  * holds them; in the in-place mode a ring of one velocity chunk does, chunk
  * after chunk), and a final kernel forms W^{n+1}, q^{n+1} and stage 2.

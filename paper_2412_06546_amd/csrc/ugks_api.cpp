@@ -609,19 +609,13 @@ bool uses_push(int dim, const ugks_gas_t *gas)
     if (asks_push(gas) || gas->mem_mode == UGKS_MEM_IN_PLACE) return true;
     return !(dim == 2 && gas->fstore == UGKS_F64);
 }
-// Whether a push handle with two buffers goes by bricks of cells (FP64 f:
-// with FP32 stage-1 sums the accumulator keeps its rounding per flux).  Two
-// workgroups have to fit a CU, and there have to be bricks for all of them in
-// a launch, as the velocities of a brick are not split over workgroups: from
-// 8,192 cells in one class, and 32,768 in the fifteen or so of the coloured
-// sweep; smaller meshes take a workgroup per cell and share of velocities
-// (9,261 cells x 2,145 in one launch: 421 us by bricks, 427 by cells; a class
-// of 32,768 cells in fifteen colours is 546 bricks, two for every CU).
-bool uses_bricks(int dim, const ugks_gas_t *gas, bool push, int nc, int ntab)
+// Whether a push handle goes by bricks of cells: the threads of a brick's
+// workgroup, or 0.  FP64 f in two buffers only; FP32 stage-1 sums and the ring
+// in place have no brick kernel.
+int uses_bricks(int dim, const ugks_gas_t *gas, bool push, int nc, int nv, int ntab)
 {
-    const bool unordered = gas->sweep == UGKS_SWEEP_PUSH_UNORDERED;
-    return push && gas->fstore == UGKS_F64 && gas->mem_mode == UGKS_MEM_TWO_BUFFERS && nc >= (unordered ? 8192 : 32768) &&
-           brick_lds_bytes(dim, ntab) <= kBrickLds;
+    if (!push || gas->fstore != UGKS_F64 || gas->mem_mode != UGKS_MEM_TWO_BUFFERS) return 0;
+    return brick_threads(dim, gas->sweep == UGKS_SWEEP_PUSH_UNORDERED, nc, nv, ntab);
 }
 
 // the push sweep's running moment sums about U^n, per cell (in place)
@@ -786,7 +780,7 @@ extern "C" int ugks_create(const ugks_mesh_t *mesh, const ugks_vgrid_t *vgrid, c
         h->tensor = detect_tensor(D, h->nv, vgrid->u, n1d, axes, kidx);
         // the per-workgroup Gaussian tables must fit in LDS next to the rest
         if (h->tensor && (size_t)(Dim<3>::MF + 1) * axes.size() * sizeof(double) > 48 * 1024) h->tensor = 0;
-        h->bricks = uses_bricks(D, gas, h->push, h->nc, h->tensor ? (int)axes.size() : 0) ? 1 : 0;
+        h->bricks = uses_bricks(D, gas, h->push, h->nc, h->nv, h->tensor ? (int)axes.size() : 0);
         if (D == 2) create_d<2>(h, S, gas);
         else create_d<3>(h, S, gas);
 
@@ -968,8 +962,8 @@ void sweep(ugks_t *h)
         hip_check(launch_sweep_inplace(h->P, h->f[0], h->n_wallf > 0, h->stream), "in-place sweep launch");
     } else if (h->push) {
         hip_check(launch_push_step(h->P, h->f[h->cur], h->f[1 - h->cur], !h->base_ok, h->colour_cells,
-                                   h->colour_off.data(), (int)h->colour_off.size() - 1, h->bricks != 0,
-                                   h->wall_cells, h->n_wall_cells, h->stream),
+                                   h->colour_off.data(), (int)h->colour_off.size() - 1, h->bricks, h->wall_cells,
+                                   h->n_wall_cells, h->stream),
                   "push sweep launch");
         h->base_ok = 1;
         h->last_push = 1;

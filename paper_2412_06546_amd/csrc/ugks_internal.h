@@ -39,11 +39,8 @@ template <int D> struct alignas(16) CellGeo {
 };
 
 // Cells of a brick of the push sweep (FP64 f): the cell lists are ordered so
-// that groups of this many consecutive entries are compact.  The LDS of a
-// brick's workgroup (tables and sums), and what of it leaves room for two
-// workgroups a CU.
-constexpr int kBrickCells = 4, kBrickThreads = 768;
-constexpr size_t kBrickLds = 80 * 1024;
+// that groups of this many consecutive entries are compact.
+constexpr int kBrickCells = 4;
 
 template <int D> struct alignas(16) FaceGeo {
     int l, r, bc, bcid;
@@ -164,7 +161,9 @@ hipError_t launch_batch_residual(const BatchItem *items, int n, int dim, hipStre
 // workgroups of the per-cell sweep grid for nc cells (a multiple of the XCD span)
 int sweep_grid(int nc);
 
-size_t brick_lds_bytes(int dim, int ntab);
+// Threads of a brick's workgroup for a push handle with FP64 f in two buffers
+// (ntab = 0: scattered velocities), or 0 where a workgroup per cell is faster.
+int brick_threads(int dim, bool unordered, int nc, int nv, int ntab);
 hipError_t launch_cfl(const Params &p, double *cell_dt, hipStream_t s);
 hipError_t launch_init(const Params &p, const double *prim0, void *f, hipStream_t s);
 hipError_t launch_moments(const Params &p, const void *f, hipStream_t s);
@@ -174,10 +173,10 @@ hipError_t launch_sweep(const Params &p, const void *f_in, void *f_out, hipStrea
 // first when need_base, then the wall cells (wall densities into rho_w and
 // the step's wall flux), then one launch per colour over cells[coff[c] ..
 // coff[c+1]) (coff: host array of ncol + 1 offsets into the device list
-// cells; bricks: in brick order, brick kernels), then stage 2
-// into f and the next base into acc
+// cells; bricks: the threads of a brick's workgroup, the list in brick order,
+// or 0), then stage 2 into f and the next base into acc
 hipError_t launch_push_step(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff,
-                            int ncol, bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s);
+                            int ncol, int bricks, const int *wall_cells, int n_wall_cells, hipStream_t s);
 // the push sweep with one f buffer (FP64 or FP32 f): the wall cells, then per
 // velocity chunk the base into the ring, one launch per colour, the stage-1
 // values back into f; then W^{n+1}, q^{n+1} and stage 2 in place

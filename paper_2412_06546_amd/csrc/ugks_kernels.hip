@@ -1819,12 +1819,14 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
 // 18.0 against 10.2 (before whole bricks were put first in the list), and
 // workgroups of 256, 512 and 1,024 threads 13.4, 10.3 and 10.3: 768 threads at
 // two workgroups a CU keep 24 wavefronts on few enough records for the scalar
-// cache.
-template <int D, bool TENSOR>
-__global__ __launch_bounds__(kBrickThreads) __attribute__((amdgpu_waves_per_eu(6))) void k_push_brick(
+// cache.  Scattered sets, whose exponentials take more registers, have two
+// workgroups of 512 threads a CU, which spill nothing (107,118 x 4,548 in one
+// launch: a step 13.98 ms, 14.86 with 768 threads and 8 spilled registers).
+template <int D, bool TENSOR, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TENSOR ? 6 : 4))) void k_push_brick(
     Params p, const double *__restrict__ fin, double *__restrict__ acc, const int *__restrict__ cells, int ncell)
 {
-    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NT = MF + 1, B = kBrickCells, BS = kBrickThreads;
+    constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NT = MF + 1, B = kBrickCells;
     extern __shared__ double smem[];
     __shared__ double sums[B][NC][BS];
     const int b = xcd_cell(blockIdx.x) * B;
@@ -3093,15 +3095,56 @@ void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_
     else launch_final_form<D, FT, TENSOR, 1024, 8>(p, f, acc, s);  // up to 16,384 velocities
 }
 
-size_t brick_lds_bytes(int dim, int ntab)
+// Workgroups of a brick launch that the chip holds at once.
+constexpr int brick_slots(bool tab, int threads) { return 256 * (4 * (tab ? 6 : 4) / (threads / 64)); }
+
+// The rule of brick_threads.  Bricks save adds but put the work of four cells
+// into one workgroup, so they gain where a launch has workgroups enough (from
+// 8,192 cells in one class, 32,768 in the coloured sweep's dozen or so) and the
+// velocities fill the lanes of the width that they fill best.  The line is put
+// by that share of lanes.  Steps by cells against bricks, in ms:
+//   3D, one class, 35,937 cells: 0.71 / 0.75 at 400 velocities (0.78 of 512
+//   lanes), 0.81 / 0.75 at 450 (0.88), 0.96 / 1.06 at 640 (0.83 of 768, one
+//   iteration), 1.04 / 1.09 at 784 (0.77 of 512), 1.24 / 1.17 at 1,000,
+//   1.37 / 1.40 at 1,152 (0.75 of 768), 1.43 / 1.40 at 1,200 (0.78), 1.81 /
+//   1.59 at 1,331, 5.1 / 4.2 at 4,548;
+//   3D in colours: 0.58 / 0.83 at 100, 1.72 / 1.77 at 1,000, 2.03 / 2.10 at
+//   1,280, 2.31 / 2.22 at 1,331 (0.87), 6.1 / 5.8 at 4,548, and 107,118 cells
+//   17.5 / 15.2 there;
+//   2D, 33,800 cells, one class: 0.27 / 0.36 at 37, 0.59 / 0.55 at 350 (0.68),
+//   0.73 / 0.61 at 512, 1.04 / 0.87 at 784, 1.90 / 1.50 at 1,331; in colours
+//   0.61 / 0.63 at 300 (0.59), 0.90 / 0.80 at 512, 2.18 / 1.78 at 1,331;
+//   scattered, 3D, one class: 1.09 / 1.18 at 784, 1.96 / 1.78 at 1,331; in
+//   colours by cells up to 9,000 velocities (6.2 / 6.4 at 4,548); 2D 1.05 /
+//   0.90 and in colours 1.26 / 1.12 at 784.
+// A workgroup's tables and sums must leave room for as many workgroups a CU
+// as its width allows.
+int brick_threads(int dim, bool unordered, int nc, int nv, int ntab)
 {
-    const size_t mf = dim == 2 ? Dim<2>::MF : Dim<3>::MF, nc = dim == 2 ? Dim<2>::NC : Dim<3>::NC;
-    return sizeof(double) * kBrickCells * ((mf + 1) * (size_t)ntab + nc * kBrickThreads);
+    const bool tab = ntab > 0;
+    if (nc < (unordered ? 8192 : 32768) || (dim == 3 && !unordered && !tab)) return 0;
+    auto share = [&](int w) { return (double)nv / ((double)w * ((nv + w - 1) / w)); };
+    const int w = !tab ? 512 : (share(768) >= share(512) || (dim == 3 && !unordered)) ? 768 : 512;
+    const bool once = nv <= w;  // one iteration
+    if (once && (!tab || (dim == 3 && !unordered))) return 0;
+    const double least = dim == 2 ? 0.65 : !unordered ? 0.85 : once ? 0.87 : 0.775;
+    const size_t mf = dim == 2 ? Dim<2>::MF : Dim<3>::MF, comp = dim == 2 ? Dim<2>::NC : Dim<3>::NC;
+    const size_t lds = sizeof(double) * kBrickCells * ((mf + 1) * (size_t)ntab + comp * w);
+    return share(w) >= least && lds * (brick_slots(tab, w) / 256) <= 160 * 1024 ? w : 0;
+}
+
+// One launch over n cells in brick order.
+template <int D, bool TENSOR, int BS>
+void launch_bricks(const Params &p, const double *fin, double *acc, const int *cells, int n, hipStream_t s)
+{
+    const size_t tables = sizeof(double) * kBrickCells * (Dim<D>::MF + 1) * (TENSOR ? p.ntab : 0);
+    hipLaunchKernelGGL((k_push_brick<D, TENSOR, BS>), dim3(sweep_grid((n + kBrickCells - 1) / kBrickCells)), dim3(BS), tables, s, p,
+                       fin, acc, cells, n);
 }
 
 template <int D, typename FT, bool TENSOR>
 hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int *cells, const int *coff, int ncol,
-                  bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
+                  int bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
 {
     constexpr int MF = Dim<D>::MF, NW = D + 2, BS = 256;
     using AT = typename AccOf<FT>::T;
@@ -3119,8 +3162,8 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
         if (n <= 0) continue;
         if constexpr (sizeof(FT) == 8) {
             if (bricks) {
-                hipLaunchKernelGGL((k_push_brick<D, TENSOR>), dim3(sweep_grid((n + kBrickCells - 1) / kBrickCells)),
-                                   dim3(kBrickThreads), tab * kBrickCells, s, p, fin, acc, cells + coff[c], n);
+                if (TENSOR && bricks == 768) launch_bricks<D, TENSOR, TENSOR ? 768 : 512>(p, fin, acc, cells + coff[c], n, s);
+                else launch_bricks<D, TENSOR, 512>(p, fin, acc, cells + coff[c], n, s);
                 continue;
             }
         }
@@ -3140,7 +3183,7 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
 
 template <int D, typename FT>
 hipError_t push_d(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff, int ncol,
-                  bool bricks, const int *wc, int nwc, hipStream_t s)
+                  int bricks, const int *wc, int nwc, hipStream_t s)
 {
     return p.ntab > 0 ? push_t<D, FT, true>(p, f, acc, need_base, cells, coff, ncol, bricks, wc, nwc, s)
                       : push_t<D, FT, false>(p, f, acc, need_base, cells, coff, ncol, bricks, wc, nwc, s);
@@ -3213,7 +3256,7 @@ hipError_t launch_push_inplace(const Params &p, void *f, const int *cells, const
 }
 
 hipError_t launch_push_step(const Params &p, void *f, void *acc, bool need_base, const int *cells, const int *coff,
-                            int ncol, bool bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
+                            int ncol, int bricks, const int *wall_cells, int n_wall_cells, hipStream_t s)
 {
     // bfloat16 f: acc holds FP32 stage-1 sums
     if (p.dim == 2)

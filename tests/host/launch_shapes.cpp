@@ -1,14 +1,12 @@
 // The launches of a time step, recorded instead of run: hipLaunchKernel is
 // defined here, so that the library's launchers hand over their grids and
-// workgroups on any machine.  Exit status 0 when every expectation holds.
-#include "ugks_internal.h"
+// workgroups on any machine.  The host file is included for the push sweep's
+// orders and colours.  Exit status 0 when every expectation holds.
+#include "../../paper_2412_06546_amd/csrc/ugks_api.cpp"
 
 #include <dlfcn.h>
 
-#include <cstdio>
-#include <cstring>
-#include <string>
-#include <vector>
+#include <map>
 
 namespace {
 
@@ -74,7 +72,7 @@ void largest_meshes()
                         const std::string what = std::to_string(dim) + "D, storage " + std::to_string(fs) + ", " +
                                                  std::to_string(nc) + " cells x " + std::to_string(nv);
                         const int all[2] = {0, nc};
-                        for (bool bricks : {false, true}) {
+                        for (int bricks : {0, 512, 768}) {
                             if (bricks && fs != 0) continue;
                             (void)ugx::launch_push_step(p, nullptr, nullptr, true, nullptr, all, 1, bricks, nullptr, 0, nullptr);
                             expect_launchable(what + ", push", nc, {"k_push_final", "k_push_base"});
@@ -92,6 +90,109 @@ void largest_meshes()
                         (void)ugx::launch_prologue(p, nullptr);
                         expect_launchable(what + ", prologue", nc, {});
                     }
+}
+
+// Bricks only where the velocities fill the lanes.
+void brick_launches()
+{
+    for (int dim : {2, 3})
+        for (bool unordered : {false, true})
+            for (int ntab : {0, 40, 75})
+                for (int nv = 1; nv <= 16384; nv += nv < 2600 ? 1 : 97) {
+                    const int w = ugx::brick_threads(dim, unordered, 1 << 20, nv, ntab);
+                    const std::string what = std::to_string(dim) + "D, " + std::to_string(nv) + " velocities, " +
+                                             std::to_string(ntab) + " table entries" + (unordered ? "" : ", colours");
+                    expect(w == 0 || w == 512 || (w == 768 && ntab), what + ": width " + std::to_string(w));
+                    if (!w) continue;
+                    const int iters = (nv + w - 1) / w;
+                    expect(nv >= (dim == 2 ? 0.65 : 0.775) * w * iters, what + ": lanes stand idle");
+                    for (int bricks : {1, 3, 44, 137, 700, 5000}) {
+                        const int all[2] = {0, 4 * bricks};
+                        const ugx::Params p = params(dim, 0, 4 * bricks, nv, ntab, 0);
+                        g_launches.clear();
+                        (void)ugx::launch_push_step(p, nullptr, nullptr, false, nullptr, all, 1, w, nullptr, 0, nullptr);
+                        expect(g_launches.size() == 2 && g_launches[0].name.find("k_push_brick") != std::string::npos,
+                               what + ": not a brick launch");
+                        const Launch &l = g_launches[0];
+                        expect((int)l.block.x == w && (int)l.grid.x >= bricks && (int)l.grid.y <= iters, what + ": shape");
+                        expect(l.lds + sizeof(double) * 4 * (dim == 2 ? 2 : 1) * w <= 80 * 1024, what + ": LDS");
+                    }
+                }
+    // small meshes, and velocity counts that leave most lanes idle
+    for (int dim : {2, 3})
+        for (int nv : {1, 37, 100, 216, 1025}) {
+            expect(ugx::brick_threads(dim, true, 8191, 4548, 40) == 0 && ugx::brick_threads(dim, false, 32767, 4548, 40) == 0,
+                   "small mesh");
+            if (dim == 3 || nv < 300)
+                expect(ugx::brick_threads(dim, true, 1 << 20, nv, 40) == 0, std::to_string(nv) + " velocities by bricks");
+        }
+}
+
+// A lattice of n^3 cells with a share of them missing: cells and neighbours
+// only, which is all that orders and colours read.
+std::vector<ugx::CellGeo<3>> holed_lattice(int n, unsigned seed, int of_16)
+{
+    std::vector<int> id((size_t)n * n * n, -1);
+    int nc = 0;
+    unsigned r = seed;
+    for (int &c : id) {
+        r = r * 1664525u + 1013904223u;
+        if ((int)(r >> 28) >= of_16) c = nc++;
+    }
+    std::vector<ugx::CellGeo<3>> g((size_t)nc);
+    for (int z = 0, t = 0; z < n; ++z)
+        for (int y = 0; y < n; ++y)
+            for (int x = 0; x < n; ++x, ++t) {
+                if (id[t] < 0) continue;
+                ugx::CellGeo<3> &c = g[id[t]];
+                std::memset(&c, 0, sizeof(c));
+                const int d[6][3] = {{1, 0, 0}, {-1, 0, 0}, {0, 1, 0}, {0, -1, 0}, {0, 0, 1}, {0, 0, -1}};
+                c.nf = 6;
+                for (int j = 0; j < 6; ++j) {  // periodic in x
+                    const int a = (x + d[j][0] + n) % n, b = y + d[j][1], e = z + d[j][2];
+                    c.nb[j] = b < 0 || b >= n || e < 0 || e >= n ? -1 : id[((size_t)e * n + b) * n + a];
+                }
+            }
+    return g;
+}
+
+// No stored cell may be written by two workgroups of a colour's launch: the
+// order of the adds into it would be open.  A workgroup takes kBrickCells
+// entries of the class, or one by cells, and writes them and their neighbours.
+void colours_write_apart()
+{
+    for (int of_16 : {0, 3, 5, 9})
+        for (int per : {1, ugx::kBrickCells}) {
+            const auto g = holed_lattice(17, 7u + of_16, of_16);
+            const int nc = (int)g.size();
+            std::vector<int> order(nc), group(nc), cells, off;
+            int n_groups = nc;
+            for (int c = 0; c < nc; ++c) order[c] = group[c] = c;
+            if (per > 1) order = brick_order<3>(g, per, group, n_groups);
+            push_colours<3>(g, order, group, n_groups, cells, off);
+            const std::string what = std::to_string(of_16) + "/16 holes, " + std::to_string(per) + " cells a workgroup";
+            std::vector<int> seen(nc, 0);
+            for (int c : cells) ++seen[c];
+            expect(std::count(seen.begin(), seen.end(), 1) == nc, what + ": every cell once");
+            std::map<int, int> sizes;
+            for (int x : group) ++sizes[x];
+            int alone = 0;
+            for (auto &s : sizes) alone += s.second == 1;
+            if (per > 1 && of_16) expect(alone > nc / 100, what + ": cells without a brick are missing from the test");
+            for (size_t k = 0; k + 1 < off.size(); ++k) {
+                std::vector<int> writer(nc, -1);
+                for (int a = off[k]; a < off[k + 1]; ++a) {
+                    const int wg = (a - off[k]) / per, c = cells[a];
+                    auto write = [&](int x) {
+                        if (x < 0) return;
+                        expect(writer[x] < 0 || writer[x] == wg, what + ": cell " + std::to_string(x) + " has two writers");
+                        writer[x] = wg;
+                    };
+                    write(c);
+                    for (int j = 0; j < g[c].nf; ++j) write(g[c].nb[j]);
+                }
+            }
+        }
 }
 
 }  // namespace
@@ -126,6 +227,8 @@ extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 int main()
 {
     largest_meshes();
+    brick_launches();
+    colours_write_apart();
     std::printf("%d checks, %d failed\n", g_checks, g_fail);
     return g_fail ? 1 : 0;
 }

@@ -51,3 +51,8 @@ def test_gather_with_prefetch_keeps_its_stencil_in_registers(spills):
             allowed = 4 if "batch" in name else 2
         assert n <= allowed, (name, n)
     assert seen == 24
+
+
+def test_bricks_spill_nothing(spills):
+    got = {k: v for k, v in spills.items() if k.startswith("k_push_brick<")}
+    assert len(got) >= 4 and not any(got.values()), got
