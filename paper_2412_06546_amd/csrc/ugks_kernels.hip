@@ -1822,9 +1822,11 @@ __device__ __forceinline__ void push_cell(const Params p, int i, const FT *__res
 // cache.  Scattered sets, whose exponentials take more registers, have two
 // workgroups of 512 threads a CU, which spill nothing (107,118 x 4,548 in one
 // launch: a step 13.98 ms, 14.86 with 768 threads and 8 spilled registers).
+// A workgroup takes the ksplit velocities of its blockIdx.y.
 template <int D, bool TENSOR, int BS>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TENSOR ? 6 : 4))) void k_push_brick(
-    Params p, const double *__restrict__ fin, double *__restrict__ acc, const int *__restrict__ cells, int ncell)
+    Params p, const double *__restrict__ fin, double *__restrict__ acc, const int *__restrict__ cells, int ncell,
+    int ksplit)
 {
     constexpr int NC = Dim<D>::NC, MF = Dim<D>::MF, NT = MF + 1, B = kBrickCells;
     extern __shared__ double smem[];
@@ -1836,6 +1838,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TENSOR ? 6 :
     const FaceGeo<D> *fg = static_cast<const FaceGeo<D> *>(p.fgeo);
     const FaceEq<D> *fe = static_cast<const FaceEq<D> *>(p.feq);
     const int nv = p.nv, ntab = TENSOR ? p.ntab : 0, nt = NT * ntab;
+    const int k0 = (int)blockIdx.y * ksplit + tid, kend = min(nv, ((int)blockIdx.y + 1) * ksplit);
     int cell[B];
 #pragma unroll
     for (int c = 0; c < B; ++c) cell[c] = c < nb ? cells[b + c] : -2;
@@ -1844,8 +1847,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TENSOR ? 6 :
             fill_tables<D, BS>(p, cg[cells[b + c]], to_prim<D>(p.W + (size_t)cells[b + c] * (D + 2)), smem + c * nt);
     __syncthreads();
     Stencil<D, double> next;
-    if (tid < nv) load_stencil<D, double>(cg[cell[0]], cell[0], fin, nv, tid, next);
-    for (int k = tid; k < nv; k += BS) {
+    if (k0 < kend) load_stencil<D, double>(cg[cell[0]], cell[0], fin, nv, k0, next);
+    for (int k = k0; k < kend; k += BS) {
 #pragma unroll
         for (int c = 0; c < B; ++c)
 #pragma unroll
@@ -1863,7 +1866,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(TENSOR ? 6 :
             const Stencil<D, double> own = next;
             {
                 const int cn = c + 1 < nb ? cells[b + c + 1] : cell[0], kk = c + 1 < nb ? k : k + BS;
-                if (kk < nv) load_stencil<D, double>(cg[cn], cn, fin, nv, kk, next);
+                if (kk < kend) load_stencil<D, double>(cg[cn], cn, fin, nv, kk, next);
             }
             double fi[NC], gri[NC][D], out[NC], ug[NC];
             slope_from<D, double>(gi, p.limiter, own, fi, gri);
@@ -3133,13 +3136,21 @@ int brick_threads(int dim, bool unordered, int nc, int nv, int ntab)
     return share(w) >= least && lds * (brick_slots(tab, w) / 256) <= 160 * 1024 ? w : 0;
 }
 
-// One launch over n cells in brick order.
+// One launch over n cells in brick order.  A class with fewer bricks than the
+// chip has slots is split over velocities, down to one iteration a workgroup:
+// greedy colouring leaves few bricks to the last classes (35,937 cells of a
+// channel: 1,436 bricks in the largest class, 137, 70, 44, 41, 3 and 2 in the
+// last six; 2,145 velocities 3.31 -> 3.27 ms a step; 107,118 x 4,548 15.26 ->
+// 15.21).
 template <int D, bool TENSOR, int BS>
 void launch_bricks(const Params &p, const double *fin, double *acc, const int *cells, int n, hipStream_t s)
 {
+    const int nb = (n + kBrickCells - 1) / kBrickCells, iters = (p.nv + BS - 1) / BS;
+    const int split = std::max(1, std::min(iters, (brick_slots(TENSOR, BS) + nb - 1) / nb));
+    const int ks = (iters + split - 1) / split * BS;
     const size_t tables = sizeof(double) * kBrickCells * (Dim<D>::MF + 1) * (TENSOR ? p.ntab : 0);
-    hipLaunchKernelGGL((k_push_brick<D, TENSOR, BS>), dim3(sweep_grid((n + kBrickCells - 1) / kBrickCells)), dim3(BS), tables, s, p,
-                       fin, acc, cells, n);
+    hipLaunchKernelGGL((k_push_brick<D, TENSOR, BS>), dim3((unsigned)sweep_grid(nb), (unsigned)((p.nv + ks - 1) / ks)),
+                       dim3(BS), tables, s, p, fin, acc, cells, n, ks);
 }
 
 template <int D, typename FT, bool TENSOR>

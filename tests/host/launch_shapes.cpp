@@ -92,7 +92,8 @@ void largest_meshes()
                     }
 }
 
-// Bricks only where the velocities fill the lanes.
+// Bricks only where the velocities fill the lanes, and a launch of few bricks
+// on as many workgroups as their velocity iterations give.
 void brick_launches()
 {
     for (int dim : {2, 3})
@@ -106,6 +107,7 @@ void brick_launches()
                     if (!w) continue;
                     const int iters = (nv + w - 1) / w;
                     expect(nv >= (dim == 2 ? 0.65 : 0.775) * w * iters, what + ": lanes stand idle");
+                    const int slots = 24 / (w / 64) * 256;
                     for (int bricks : {1, 3, 44, 137, 700, 5000}) {
                         const int all[2] = {0, 4 * bricks};
                         const ugx::Params p = params(dim, 0, 4 * bricks, nv, ntab, 0);
@@ -115,6 +117,8 @@ void brick_launches()
                                what + ": not a brick launch");
                         const Launch &l = g_launches[0];
                         expect((int)l.block.x == w && (int)l.grid.x >= bricks && (int)l.grid.y <= iters, what + ": shape");
+                        expect((int)l.grid.y * bricks >= std::min(iters * bricks, slots) / 2,
+                               what + ": " + std::to_string(bricks) + " bricks leave the chip idle");
                         expect(l.lds + sizeof(double) * 4 * (dim == 2 ? 2 : 1) * w <= 80 * 1024, what + ": LDS");
                     }
                 }
