@@ -2488,7 +2488,8 @@ __device__ __forceinline__ void macro_from_shift(const Params &p, const double (
 // The push sweep's per-cell kernels: one workgroup per cell, thread t holding
 // the velocity pairs t, t + BS, ... of its slab in registers (NP pairs at
 // most; every velocity count a handle takes fits one of the forms of
-// launch_final).  The final kernel loads the whole stage-1 slab in one go --
+// launch_final; of the eight pairs of the widest form 8 to 82 registers are
+// spilled, in the 128 that its 1,024 threads leave).  The final kernel loads the whole stage-1 slab in one go --
 // every load of a thread in flight together -- takes its moments about U^n
 // (orders 0-3 of h, 0-1 of b), from which one wavefront forms W^{n+1},
 // tau^{n+1} and the heat flux about U^{n+1} (macro_from_shift), and applies
@@ -3070,6 +3071,10 @@ __global__ __launch_bounds__(256) void k_push_final_inplace(Params p, FT *__rest
 // thread: at 4,548 velocities 5 pairs in 512 threads 3.27 ms, 10 in 256 3.32,
 // 20 in 128 3.72 (107,118 cells, FP64, before the points came from LDS), and
 // held to more waves a SIMD than its 117 registers allow it spills (4.8-6.7).
+// Above 5,120 velocities 1,024 threads take three, five or eight pairs: with
+// eight alone, 5,200 velocities in 2D left five of them empty and spilled (a
+// step of 12,800 cells: FP32 1.93 -> 1.68 ms, BF16 2.01 -> 1.70, FP64 2.31 ->
+// 2.05; 2,744 cells x 9,000 in 3D FP64 0.90 -> 0.87).
 template <int D, typename FT, bool TENSOR, int BS>
 void launch_base_form(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
@@ -3095,6 +3100,8 @@ void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_
     if (p.nv <= 1536) launch_final_form<D, FT, TENSOR, 256, 3>(p, f, acc, s);
     else if (p.nv <= 3072) launch_final_form<D, FT, TENSOR, 512, 3>(p, f, acc, s);
     else if (p.nv <= 5120) launch_final_form<D, FT, TENSOR, 512, 5>(p, f, acc, s);
+    else if (p.nv <= 6144) launch_final_form<D, FT, TENSOR, 1024, 3>(p, f, acc, s);
+    else if (p.nv <= 10240) launch_final_form<D, FT, TENSOR, 1024, 5>(p, f, acc, s);
     else launch_final_form<D, FT, TENSOR, 1024, 8>(p, f, acc, s);  // up to 16,384 velocities
 }
 

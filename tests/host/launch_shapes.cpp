@@ -92,6 +92,30 @@ void largest_meshes()
                     }
 }
 
+// The final kernel's form holds the slab with few pairs left empty.
+void final_forms()
+{
+    for (int dim : {2, 3})
+        for (int fs : {0, 1, 2})
+            for (int nv = 1; nv <= 16384; ++nv) {
+                const ugx::Params p = params(dim, fs, 400, nv, 0, 0);
+                g_launches.clear();
+                (void)ugx::launch_push_step(p, nullptr, nullptr, false, nullptr, nullptr, 0, 0, nullptr, 0, nullptr);
+                if (g_launches.size() != 1) {
+                    expect(false, "one launch of a step without colours");
+                    return;
+                }
+                const std::string &n = g_launches[0].name;
+                const int bs = (int)g_launches[0].block.x;
+                int pairs = 0;
+                for (int np : {3, 5, 8})
+                    if (n.find("ELi" + std::to_string(bs) + "ELi" + std::to_string(np) + "EEEv") != std::string::npos) pairs = np;
+                expect(2 * bs * pairs >= nv, std::to_string(nv) + " velocities do not fit " + n);
+                if (nv > 3072) expect(2 * bs * (pairs - 3) < nv, std::to_string(nv) + " velocities leave pairs empty in " + n);
+            }
+    g_launches.clear();
+}
+
 // Bricks only where the velocities fill the lanes, and a launch of few bricks
 // on as many workgroups as their velocity iterations give.
 void brick_launches()
@@ -231,6 +255,7 @@ extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 int main()
 {
     largest_meshes();
+    final_forms();
     brick_launches();
     colours_write_apart();
     std::printf("%d checks, %d failed\n", g_checks, g_fail);

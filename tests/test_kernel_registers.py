@@ -56,3 +56,14 @@ def test_gather_with_prefetch_keeps_its_stencil_in_registers(spills):
 def test_bricks_spill_nothing(spills):
     got = {k: v for k, v in spills.items() if k.startswith("k_push_brick<")}
     assert len(got) >= 4 and not any(got.values()), got
+
+
+def test_final_kernels_hold_their_pairs(spills):
+    """Up to five pairs a thread nothing is spilled, but for 4 registers of 2D
+    FP64 with 1,024 threads; the last form (10,241 velocities and more) spills."""
+    got = {k: v for k, v in spills.items() if k.startswith("k_push_final<")}
+    assert len(got) == 72
+    for name, n in got.items():
+        if name.endswith(", 8>"):
+            continue
+        assert n <= (4 if name == "k_push_final<2, double, true, 1024, 5>" else 0), (name, n)
