@@ -3131,16 +3131,20 @@ constexpr int brick_slots(bool tab, int threads) { return 256 * (4 * (tab ? 6 : 
 // as its width allows.
 int brick_threads(int dim, bool unordered, int nc, int nv, int ntab)
 {
-    const bool tab = ntab > 0;
-    if (nc < (unordered ? 8192 : 32768) || (dim == 3 && !unordered && !tab)) return 0;
-    auto share = [&](int w) { return (double)nv / ((double)w * ((nv + w - 1) / w)); };
-    const int w = !tab ? 512 : (share(768) >= share(512) || (dim == 3 && !unordered)) ? 768 : 512;
-    const bool once = nv <= w;  // one iteration
-    if (once && (!tab || (dim == 3 && !unordered))) return 0;
-    const double least = dim == 2 ? 0.65 : !unordered ? 0.85 : once ? 0.87 : 0.775;
+    const bool tab = ntab > 0, colours3 = dim == 3 && !unordered;
+    if (nc < (unordered ? 8192 : 32768) || (colours3 && !tab)) return 0;
     const size_t mf = dim == 2 ? Dim<2>::MF : Dim<3>::MF, comp = dim == 2 ? Dim<2>::NC : Dim<3>::NC;
-    const size_t lds = sizeof(double) * kBrickCells * ((mf + 1) * (size_t)ntab + comp * w);
-    return share(w) >= least && lds * (brick_slots(tab, w) / 256) <= 160 * 1024 ? w : 0;
+    auto share = [&](int w) {  // of the lanes, 0 where the LDS does not do
+        const size_t lds = sizeof(double) * kBrickCells * ((mf + 1) * (size_t)ntab + comp * w);
+        if (lds * (brick_slots(tab, w) / 256) > 160 * 1024) return 0.0;
+        return (double)nv / ((double)w * ((nv + w - 1) / w));
+    };
+    const double s512 = colours3 ? 0.0 : share(512), s768 = tab ? share(768) : 0.0;
+    const int w = 1.05 * s768 >= s512 ? 768 : 512;
+    const bool once = nv <= w;  // one iteration
+    if (once && (!tab || colours3)) return 0;
+    const double least = dim == 2 ? 0.65 : !unordered ? 0.85 : once ? 0.87 : 0.775;
+    return (w == 768 ? s768 : s512) >= least ? w : 0;
 }
 
 // One launch over n cells in brick order.  A class with fewer bricks than the

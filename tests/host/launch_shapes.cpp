@@ -146,6 +146,10 @@ void brick_launches()
                         expect(l.lds + sizeof(double) * 4 * (dim == 2 ? 2 : 1) * w <= 80 * 1024, what + ": LDS");
                     }
                 }
+    // 5,600 velocities fill 512 threads better, but with 154 table entries in
+    // 2D only the tables and sums of 768 leave room for all their workgroups
+    expect(ugx::brick_threads(2, true, 12800, 5600, 154) == 768 && ugx::brick_threads(2, true, 12800, 5600, 120) == 512,
+           "width by LDS");
     // small meshes, and velocity counts that leave most lanes idle
     for (int dim : {2, 3})
         for (int nv : {1, 37, 100, 216, 1025}) {
