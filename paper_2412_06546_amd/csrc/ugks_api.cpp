@@ -1085,16 +1085,18 @@ extern "C" int ugks_macros(ugks_t *h, double *W_out, double *q_out)
 {
     if (!h) return UGKS_ERR_ARG;
     try {
-        const size_t nc = h->nc, NW = h->dim + 2, D = h->dim, n = nc * (NW + D);
-        // W and q in one copy: through the handle's pinned memory where they
-        // are small, else through a buffer of this call
+        const size_t nc = h->nc, NW = h->dim + 2, D = h->dim;
+        // what is asked for of W and q behind it, in one copy: through the
+        // handle's pinned memory where they are small, else through a buffer
+        // of this call (nothing asked for: n = 0)
+        const size_t from = W_out ? 0 : nc * NW, n = nc * (q_out ? NW + D : NW) - from;
         std::unique_ptr<double[]> own;
-        if (!h->h_macro) own.reset(new double[n]);
+        if (n && !h->h_macro) own.reset(new double[n]);
         double *buf = h->h_macro ? h->h_macro : own.get();
-        hip_check(hipMemcpyAsync(buf, h->W, sizeof(double) * n, hipMemcpyDeviceToHost, h->stream), "copy W and q");
+        if (n) hip_check(hipMemcpyAsync(buf, h->W + from, sizeof(double) * n, hipMemcpyDeviceToHost, h->stream), "copy W and q");
         hip_check(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
-        const double *W = buf, *q = buf + nc * NW;
-        for (size_t i = 0; i < nc; ++i) {
+        const double *W = buf, *q = buf + (nc * NW - from);
+        for (size_t i = 0; n && i < nc; ++i) {
             const size_t c = h->cell_of[i];
             if (W_out) std::copy(&W[i * NW], &W[i * NW] + NW, W_out + c * NW);
             if (q_out) std::copy(&q[i * D], &q[i * D] + D, q_out + c * D);

@@ -1,6 +1,6 @@
 // The launches of a time step, recorded instead of run: hipLaunchKernel is
 // defined here, so that the library's launchers hand over their grids and
-// workgroups on any machine.  The host file is included for the push sweep's
+// workgroups on any machine; copies are made between host arrays.  The host file is included for the push sweep's
 // orders and colours.  Exit status 0 when every expectation holds.
 #include "../../paper_2412_06546_amd/csrc/ugks_api.cpp"
 
@@ -16,6 +16,7 @@ struct Launch {
     size_t lds;
 };
 std::vector<Launch> g_launches;
+size_t g_copied = 0;  // bytes of the copies since it was cleared
 int g_checks = 0, g_fail = 0;
 
 void expect(bool ok, const std::string &what)
@@ -227,6 +228,39 @@ void colours_write_apart()
         }
 }
 
+// The read-out copies what it is asked for, and puts it in the caller's order.
+void read_out()
+{
+    for (int dim : {2, 3})
+        for (bool pinned : {false, true}) {
+            const int nc = 70, NW = dim + 2;
+            ugks h;
+            h.dim = dim;
+            h.nc = nc;
+            std::vector<double> state((size_t)nc * (NW + dim)), staging(state.size());
+            for (size_t i = 0; i < state.size(); ++i) state[i] = 1.0 + (double)i;
+            for (int i = 0; i < nc; ++i) h.cell_of.push_back((i * 33) % nc);
+            h.W = state.data();
+            h.q = h.W + (size_t)nc * NW;
+            h.h_macro = pinned ? staging.data() : nullptr;
+            for (int ask = 0; ask < 4; ++ask) {
+                std::vector<double> W((size_t)nc * NW, -1.0), q((size_t)nc * dim, -1.0);
+                g_copied = 0;
+                expect(ugks_macros(&h, ask & 1 ? W.data() : nullptr, ask & 2 ? q.data() : nullptr) == UGKS_OK, "macros");
+                const std::string what = std::to_string(dim) + "D read-out " + std::to_string(ask);
+                expect(g_copied == sizeof(double) * nc * ((ask & 1 ? NW : 0) + (ask & 2 ? dim : 0)),
+                       what + " copies " + std::to_string(g_copied) + " bytes");
+                for (int i = 0; i < nc; ++i) {
+                    const int c = h.cell_of[i];
+                    for (int m = 0; m < NW; ++m)
+                        expect(W[(size_t)c * NW + m] == (ask & 1 ? h.W[(size_t)i * NW + m] : -1.0), what + ": W");
+                    for (int d = 0; d < dim; ++d)
+                        expect(q[(size_t)c * dim + d] == (ask & 2 ? h.q[(size_t)i * dim + d] : -1.0), what + ": q");
+                }
+            }
+        }
+}
+
 }  // namespace
 
 // A launch is pushed with its shape, popped by the kernel's host stub, and
@@ -255,6 +289,13 @@ extern "C" hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3 block,
     return hipSuccess;
 }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+extern "C" hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKind, hipStream_t)
+{
+    g_copied += bytes;
+    std::memcpy(to, from, bytes);
+    return hipSuccess;
+}
+extern "C" hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 
 int main()
 {
@@ -262,6 +303,7 @@ int main()
     final_forms();
     brick_launches();
     colours_write_apart();
+    read_out();
     std::printf("%d checks, %d failed\n", g_checks, g_fail);
     return g_fail ? 1 : 0;
 }
