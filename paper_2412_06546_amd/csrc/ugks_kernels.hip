@@ -2485,45 +2485,63 @@ __device__ __forceinline__ void macro_from_shift(const Params &p, const double (
 }
 
 // ------------------------------------------------------------------------
-// The push sweep's per-cell kernels: one workgroup per cell, thread t holding
-// the velocity pairs t, t + BS, ... of its slab in registers (NP pairs at
-// most; every velocity count a handle takes fits one of the forms of
-// launch_final; of the eight pairs of the widest form 8 to 82 registers are
-// spilled, in the 128 that its 1,024 threads leave).  The final kernel loads the whole stage-1 slab in one go --
-// every load of a thread in flight together -- takes its moments about U^n
-// (orders 0-3 of h, 0-1 of b), from which one wavefront forms W^{n+1},
-// tau^{n+1} and the heat flux about U^{n+1} (macro_from_shift), and applies
-// stage 2 from the registers into f and the next step's base into acc, so
-// that the slab is read once.  The base kernel takes the velocities in the
-// same order and reduces the same way, so both give the same bits.  Bound by
-// the latency of a cell's phases at two workgroups a CU (VALUs half busy);
-// 107,118 cells x 4,548: 3.78 -> 2.90 ms in FP64 (11.7 GB, 4.0 TB/s), 3.27 ->
-// 3.00 in FP32; 50,688 x 13,824 in FP64 7.36 -> 4.95 ms; against one wavefront
-// per cell (and FP64 slabs of at most 24 values in 256 threads), butterfly
-// sums and the points read from memory in both passes.
+// The push sweep's per-cell kernels: one workgroup per cell, thread t taking
+// the velocity pairs t, t + BS, ... of its slab.  The final kernel takes the
+// moments of the stage-1 slab about U^n (orders 0-3 of h, 0-1 of b), from
+// which one wavefront forms W^{n+1}, tau^{n+1} and the heat flux about U^{n+1}
+// (macro_from_shift), and applies stage 2 into f and the next step's base into
+// acc.  The base kernel takes the velocities in the same order and reduces the
+// same way, so both give the same bits.
+//
+// FP64 stage-1 sums are loaded in one go into registers -- every load of a
+// thread in flight together -- and the slab is read once: NP pairs a thread at
+// most, every velocity count a handle takes fits one of the forms of
+// launch_final (of the eight pairs of the widest, up to 18 registers are
+// spilled in 2D in the 128 that its 1,024 threads leave).  Bound by the latency of a
+// cell's phases at two workgroups a CU (VALUs half busy); 107,118 cells x
+// 4,548: 3.78 -> 2.90 ms (11.7 GB, 4.0 TB/s); 50,688 x 13,824 7.36 -> 4.95 ms;
+// against one wavefront per cell (and slabs of at most 24 values in 256
+// threads), butterfly sums and the points read from memory in both passes.
+//
+// FP32 stage-1 sums (FP32 and BF16 f) are read again in the second pass (NP =
+// 0): half the bytes, found in L2, and workgroups of few wavefronts and registers
+// (held to six waves a SIMD, five for scattered BF16, which spills at six)
+// overlap the phases of more cells on a CU.  The final kernel with the slab in
+// registers / read again, FP32 f: 16,200 cells in 2D x 2,145 396 / 328 us, x
+// 3,600 553 / 491; 64,000 in 3D x 100 297 / 126; a step of 19,683 in 3D x 6,000
+// 2,751 / 2,394 us, BF16 2,755 / 2,328.
 // ------------------------------------------------------------------------
 // Elements k, k + 1 of an array of n (k < n): one access where the pair is
 // aligned (pairs from even elements of slabs that start at even elements),
-// else two; zero past the end.
+// else two, of k and k + step; zero past the end.
 template <typename T>
-__device__ __forceinline__ void load_pair(const T *__restrict__ q, int k, int n, bool aligned, double &a, double &b)
+__device__ __forceinline__ void load_pair(const T *__restrict__ q, int k, int n, bool aligned, double &a, double &b,
+                                          int step = 1)
 {
     if (aligned) {
         load2<T>(q + k, a, b);
     } else {
         a = to_f64(q[k]);
-        b = k + 1 < n ? to_f64(q[k + 1]) : 0.0;
+        b = k + step < n ? to_f64(q[k + step]) : 0.0;
     }
 }
 template <typename T>
-__device__ __forceinline__ void store_pair(T *__restrict__ q, int k, int n, bool aligned, T a, T b)
+__device__ __forceinline__ void store_pair(T *__restrict__ q, int k, int n, bool aligned, T a, T b, int step = 1)
 {
     if (aligned) {
         store2<T>(q + k, a, b);
     } else {
         q[k] = a;
-        if (k + 1 < n) q[k + 1] = b;
+        if (k + step < n) q[k + step] = b;
     }
+}
+
+// The first velocity of a thread's j-th pair in a slab: neighbours where pairs
+// are aligned, else two a workgroup's width apart, so that the single accesses
+// of a wavefront still lie side by side.
+template <int BS> __device__ __forceinline__ int pair_first(int j, bool aligned)
+{
+    return aligned ? 2 * ((int)threadIdx.x + BS * j) : (int)threadIdx.x + 2 * BS * j;
 }
 
 // A velocity pair's weights (zero past the last velocity) and, where the set
@@ -2534,15 +2552,15 @@ __device__ __forceinline__ void store_pair(T *__restrict__ q, int k, int n, bool
 template <int D, bool TENSOR> struct VelPair {
     double w[2], u[TENSOR ? 1 : 2][D];
     unsigned kx[2];
-    // velocities k0, k0 + 1 of those below n
-    __device__ __forceinline__ void load(const Params &p, int k0, int n, bool aligned)
+    // velocities k0, k0 + 1 (not aligned: k0 + step) of those below n
+    __device__ __forceinline__ void load(const Params &p, int k0, int n, bool aligned, int step = 1)
     {
-        load_pair<double>(p.w, k0, n, aligned, w[0], w[1]);
+        load_pair<double>(p.w, k0, n, aligned, w[0], w[1], step);
         kx[0] = kx[1] = 0u;
         if constexpr (TENSOR) {
             if (!aligned) {
                 kx[0] = (unsigned)p.kidx[k0];
-                if (k0 + 1 < n) kx[1] = (unsigned)p.kidx[k0 + 1];
+                if (k0 + step < n) kx[1] = (unsigned)p.kidx[k0 + step];
             } else {
                 const int2 x = *reinterpret_cast<const int2 *>(p.kidx + k0);
                 kx[0] = (unsigned)x.x;
@@ -2550,7 +2568,7 @@ template <int D, bool TENSOR> struct VelPair {
             }
         } else {
 #pragma unroll
-            for (int d = 0; d < D; ++d) load_pair<double>(p.u + (size_t)d * p.nv, k0, n, aligned, u[0][d], u[1][d]);
+            for (int d = 0; d < D; ++d) load_pair<double>(p.u + (size_t)d * p.nv, k0, n, aligned, u[0][d], u[1][d], step);
         }
     }
     // peculiar velocity of element e: from the table of u_d - U_d, or the points
@@ -2668,12 +2686,12 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
 #pragma unroll
     for (int m = 0; m < NW; ++m) mom[m] = 0.0;
 #pragma unroll 2
-    for (int k0 = 2 * tid; k0 < nv; k0 += 2 * BS) {
+    for (int k0 = pair_first<BS>(0, aligned); k0 < nv; k0 += 2 * BS) {
         double f[NC][2];
         VelPair<D, TENSOR> vp;
-        vp.load(p, k0, nv, aligned);
+        vp.load(p, k0, nv, aligned, BS);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) load_pair<FT>(fin + base + (size_t)c * nv, k0, nv, aligned, f[c][0], f[c][1]);
+        for (int c = 0; c < NC; ++c) load_pair<FT>(fin + base + (size_t)c * nv, k0, nv, aligned, f[c][0], f[c][1], BS);
         AT sv[NC][2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -2688,7 +2706,7 @@ __global__ __launch_bounds__(BS) void k_push_base(Params p, const FT *__restrict
             add_moments<D>(mom, vp.w[e], c3, c2, bv[0], NC > 1 ? bv[NC - 1] : 0.0);
         }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, sv[c][0], sv[c][1]);
+        for (int c = 0; c < NC; ++c) store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, sv[c][0], sv[c][1], BS);
     }
     wave_sums<NW>(mom);
     if ((tid & 63) == 0)
@@ -2738,7 +2756,7 @@ __device__ __forceinline__ void group_macro(const Params &p, int i, const double
 }
 
 template <int D, typename FT, bool TENSOR, int BS, int NP>
-__global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fout, typename AccOf<FT>::T *__restrict__ acc)
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(NP > 0 ? 1 : (TENSOR || sizeof(FT) == 4 ? 6 : 5)))) void k_push_final(Params p, FT *__restrict__ fout, typename AccOf<FT>::T *__restrict__ acc)
 {
     using AT = typename AccOf<FT>::T;
     constexpr int NC = Dim<D>::NC, NW = D + 2, N = Shift<D>::N;
@@ -2757,27 +2775,30 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
     const Prim<D> pn = to_prim<D>(Wn);
 
     // pass 1: the slab into registers, in its storage precision (all loads
-    // issued before any use), its moments about U^n
-    AT v[NP][NC][2];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int k0 = 2 * (tid + BS * j);
+    // issued before any use), its moments about U^n; without register pairs
+    // each pass loads a pair as it comes to it
+    constexpr bool REG = NP > 0;
+    AT v[REG ? NP : 1][NC][2];
+    auto load_slab = [&](int k0, AT (&x)[NC][2]) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            v[j][c][0] = v[j][c][1] = from_f64<AT>(0.0);
+            x[c][0] = x[c][1] = from_f64<AT>(0.0);
             if (k0 < nv) {
                 const AT *q = acc + base + (size_t)c * nv + k0;
                 if (!aligned) {
-                    v[j][c][0] = q[0];
-                    if (k0 + 1 < nv) v[j][c][1] = q[1];
+                    x[c][0] = q[0];
+                    if (k0 + BS < nv) x[c][1] = q[BS];
                 } else {
-                    const typename Vec2<AT>::T x = *reinterpret_cast<const typename Vec2<AT>::T *>(q);
-                    v[j][c][0] = x.x;
-                    v[j][c][1] = x.y;
+                    const typename Vec2<AT>::T y = *reinterpret_cast<const typename Vec2<AT>::T *>(q);
+                    x[c][0] = y.x;
+                    x[c][1] = y.y;
                 }
             }
         }
-    }
+    };
+    if constexpr (REG)
+#pragma unroll
+        for (int j = 0; j < NP; ++j) load_slab(pair_first<BS>(j, aligned), v[j]);
     if constexpr (TENSOR) {
         fill_points<BS>(p, pn.U[0], pn.U[1], pn.U[D - 1], tc);
         __syncthreads();
@@ -2785,17 +2806,19 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
     double mm[N];
 #pragma unroll
     for (int t = 0; t < N; ++t) mm[t] = 0.0;
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int k0 = 2 * (tid + BS * j);
+#pragma unroll REG ? NP : 1
+    for (int j = 0; REG ? j < NP : pair_first<BS>(j, aligned) < nv; ++j) {
+        const int k0 = pair_first<BS>(j, aligned);
+        AT (&x)[NC][2] = v[REG ? j : 0];
+        if constexpr (!REG) load_slab(k0, x);
         if (k0 < nv) {
             VelPair<D, TENSOR> vp;
-            vp.load(p, k0, nv, aligned);
+            vp.load(p, k0, nv, aligned, BS);
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 double c[D], c2;
                 vp.peculiar_of(e, tc, pn.U, c, c2);
-                add_shift_moments<D>(mm, vp.w[e], c, c2, to_f64(v[j][0][e]), NC > 1 ? to_f64(v[j][NC - 1][e]) : 0.0);
+                add_shift_moments<D>(mm, vp.w[e], c, c2, to_f64(x[0][e]), NC > 1 ? to_f64(x[NC - 1][e]) : 0.0);
             }
         }
     }
@@ -2825,16 +2848,18 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
         __syncthreads();
     }
 
-    // pass 2: stage 2 from the registers into f, the next base into acc
+    // pass 2: stage 2 into f, the next base into acc
     double mb[NW];
 #pragma unroll
     for (int m = 0; m < NW; ++m) mb[m] = 0.0;
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-        const int k0 = 2 * (tid + BS * j);
+#pragma unroll REG ? NP : 1
+    for (int j = 0; REG ? j < NP : pair_first<BS>(j, aligned) < nv; ++j) {
+        const int k0 = pair_first<BS>(j, aligned);
+        AT (&x)[NC][2] = v[REG ? j : 0];
+        if constexpr (!REG) load_slab(k0, x);
         if (k0 < nv) {
             VelPair<D, TENSOR> vp;
-            vp.load(p, k0, nv, aligned);
+            vp.load(p, k0, nv, aligned, BS);
             FT fo[NC][2];
             AT bo[NC][2];
 #pragma unroll
@@ -2844,7 +2869,7 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
                 shakhov_at<D>(c3, c2, lam, shk, q1, bh, H, fp[0], fp[1]);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
-                    fo[c][e] = from_f64<FT>((to_f64(v[j][c][e]) + a1 * fp[c]) * inv1);
+                    fo[c][e] = from_f64<FT>((to_f64(x[c][e]) + a1 * fp[c]) * inv1);
                     // the base from f^{n+1} as stored (bitwise what the base
                     // kernel computes from it after a restart)
                     const double fd = opaque(to_f64(fo[c][e]));
@@ -2855,8 +2880,8 @@ __global__ __launch_bounds__(BS) void k_push_final(Params p, FT *__restrict__ fo
             }
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                store_pair<FT>(fout + base + (size_t)c * nv, k0, nv, aligned, fo[c][0], fo[c][1]);
-                store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, bo[c][0], bo[c][1]);
+                store_pair<FT>(fout + base + (size_t)c * nv, k0, nv, aligned, fo[c][0], fo[c][1], BS);
+                store_pair<AT>(acc + base + (size_t)c * nv, k0, nv, aligned, bo[c][0], bo[c][1], BS);
             }
         }
     }
@@ -3067,24 +3092,43 @@ __global__ __launch_bounds__(256) void k_push_final_inplace(Params p, FT *__rest
 // launch per colour (split over velocities when small), the final kernel
 // ------------------------------------------------------------------------
 // The form of the per-cell kernels for a velocity count: workgroup size and
-// pairs per thread.  Larger slabs take more threads rather than more pairs a
+// pairs per thread of FP64 sums.  Larger slabs take more threads rather than more pairs a
 // thread: at 4,548 velocities 5 pairs in 512 threads 3.27 ms, 10 in 256 3.32,
 // 20 in 128 3.72 (107,118 cells, FP64, before the points came from LDS), and
 // held to more waves a SIMD than its 117 registers allow it spills (4.8-6.7).
 // Above 5,120 velocities 1,024 threads take three, five or eight pairs: with
 // eight alone, 5,200 velocities in 2D left five of them empty and spilled (a
-// step of 12,800 cells: FP32 1.93 -> 1.68 ms, BF16 2.01 -> 1.70, FP64 2.31 ->
-// 2.05; 2,744 cells x 9,000 in 3D FP64 0.90 -> 0.87).
+// step of 12,800 cells 2.31 -> 2.05 ms; 2,744 cells x 9,000 in 3D 0.90 -> 0.87).
 template <int D, typename FT, bool TENSOR, int BS>
 void launch_base_form(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
     const size_t lds = sizeof(double) * ((TENSOR ? 2 * (size_t)p.ntab : 0) + (BS / 64) * (D + 2));
     hipLaunchKernelGGL((k_push_base<D, FT, TENSOR, BS>), cell_grid(p.nc, BS), dim3(BS), lds, s, p, f, acc);
 }
+// Threads of a workgroup with FP32 stage-1 sums: one, two or four wavefronts by
+// the velocities, and up to eight on meshes with too few cells to fill the chip
+// so (steps with 64, 128, 256 and 512 threads, in us: 19,683 cells in 3D x 1,331
+// 674, 686, 718, -; 7,200 in 2D x 400 98, 101, 109, 132; x 1,331 284, 279, 282,
+// 302; x 3,501 783, 736, 742, 759; x 6,000 1,119, 1,093, 1,043, 1,059; 512 in 3D
+// x 2,145 91, 84, 80, 79; 1,331 x 400 61, 60, 60, 66).  Long tables: at least
+// four, so that the LDS leaves room for sixteen wavefronts a CU.
+inline int stream_threads(const Params &p)
+{
+    int t = p.nv <= 1024 || (p.nv <= 2560 && p.nc >= 10240) ? 64 : (p.nv <= 5120 ? 128 : 256);
+    while (t < 512 && (long)p.nc * t < 160 * 1024 && 2 * t < p.nv) t *= 2;
+    return p.ntab > 256 ? std::max(t, 256) : t;
+}
+
 template <int D, typename FT, bool TENSOR>
 void launch_base(const Params &p, const FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
-    if (p.nv <= 1536) launch_base_form<D, FT, TENSOR, 256>(p, f, acc, s);
+    if constexpr (sizeof(typename AccOf<FT>::T) == 4) {
+        const int t = stream_threads(p);
+        if (t == 64) launch_base_form<D, FT, TENSOR, 64>(p, f, acc, s);
+        else if (t == 128) launch_base_form<D, FT, TENSOR, 128>(p, f, acc, s);
+        else if (t == 256) launch_base_form<D, FT, TENSOR, 256>(p, f, acc, s);
+        else launch_base_form<D, FT, TENSOR, 512>(p, f, acc, s);
+    } else if (p.nv <= 1536) launch_base_form<D, FT, TENSOR, 256>(p, f, acc, s);
     else if (p.nv <= 5120) launch_base_form<D, FT, TENSOR, 512>(p, f, acc, s);
     else launch_base_form<D, FT, TENSOR, 1024>(p, f, acc, s);
 }
@@ -3097,7 +3141,13 @@ void launch_final_form(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipSt
 template <int D, typename FT, bool TENSOR>
 void launch_final(const Params &p, FT *f, typename AccOf<FT>::T *acc, hipStream_t s)
 {
-    if (p.nv <= 1536) launch_final_form<D, FT, TENSOR, 256, 3>(p, f, acc, s);
+    if constexpr (sizeof(typename AccOf<FT>::T) == 4) {
+        const int t = stream_threads(p);
+        if (t == 64) launch_final_form<D, FT, TENSOR, 64, 0>(p, f, acc, s);
+        else if (t == 128) launch_final_form<D, FT, TENSOR, 128, 0>(p, f, acc, s);
+        else if (t == 256) launch_final_form<D, FT, TENSOR, 256, 0>(p, f, acc, s);
+        else launch_final_form<D, FT, TENSOR, 512, 0>(p, f, acc, s);
+    } else if (p.nv <= 1536) launch_final_form<D, FT, TENSOR, 256, 3>(p, f, acc, s);
     else if (p.nv <= 3072) launch_final_form<D, FT, TENSOR, 512, 3>(p, f, acc, s);
     else if (p.nv <= 5120) launch_final_form<D, FT, TENSOR, 512, 5>(p, f, acc, s);
     else if (p.nv <= 6144) launch_final_form<D, FT, TENSOR, 1024, 3>(p, f, acc, s);

@@ -93,13 +93,15 @@ void largest_meshes()
                     }
 }
 
-// The final kernel's form holds the slab with few pairs left empty.
+// The final kernel: FP64 sums in a form that holds the slab with few pairs left
+// empty, FP32 sums in workgroups of few wavefronts, more of them on a small mesh
+// or with long tables.
 void final_forms()
 {
     for (int dim : {2, 3})
         for (int fs : {0, 1, 2})
             for (int nv = 1; nv <= 16384; ++nv) {
-                const ugx::Params p = params(dim, fs, 400, nv, 0, 0);
+                const ugx::Params p = params(dim, fs, 20000, nv, 0, 0);
                 g_launches.clear();
                 (void)ugx::launch_push_step(p, nullptr, nullptr, false, nullptr, nullptr, 0, 0, nullptr, 0, nullptr);
                 if (g_launches.size() != 1) {
@@ -108,12 +110,27 @@ void final_forms()
                 }
                 const std::string &n = g_launches[0].name;
                 const int bs = (int)g_launches[0].block.x;
+                if (fs) {
+                    expect(bs == (nv <= 2560 ? 64 : nv <= 5120 ? 128 : 256) && n.find("ELi" + std::to_string(bs) + "ELi0EEEv") != std::string::npos,
+                           std::to_string(nv) + " velocities, FP32 sums: " + n);
+                    continue;
+                }
                 int pairs = 0;
                 for (int np : {3, 5, 8})
                     if (n.find("ELi" + std::to_string(bs) + "ELi" + std::to_string(np) + "EEEv") != std::string::npos) pairs = np;
                 expect(2 * bs * pairs >= nv, std::to_string(nv) + " velocities do not fit " + n);
                 if (nv > 3072) expect(2 * bs * (pairs - 3) < nv, std::to_string(nv) + " velocities leave pairs empty in " + n);
             }
+    g_launches.clear();
+    auto width = [&](int nc, int nv, int ntab) {
+        g_launches.clear();
+        (void)ugx::launch_push_step(params(2, 1, nc, nv, ntab, 0), nullptr, nullptr, true, nullptr, nullptr, 0, 0, nullptr, 0,
+                                    nullptr);
+        expect(g_launches.size() == 2 && g_launches[0].block.x == g_launches[1].block.x, "base and final kernel alike");
+        return (int)g_launches[1].block.x;
+    };
+    expect(width(20000, 400, 800) == 256, "long tables");
+    expect(width(512, 2145, 60) == 512 && width(512, 200, 60) == 128 && width(1331, 400, 60) == 128, "small mesh");
     g_launches.clear();
 }
 

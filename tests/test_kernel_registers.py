@@ -59,11 +59,11 @@ def test_bricks_spill_nothing(spills):
 
 
 def test_final_kernels_hold_their_pairs(spills):
-    """Up to five pairs a thread nothing is spilled, but for 4 registers of 2D
-    FP64 with 1,024 threads; the last form (10,241 velocities and more) spills."""
+    """FP64 sums: up to five pairs a thread nothing is spilled; the last form
+    (10,241 velocities and more) spills.  FP32 sums: at most 5 registers of
+    scattered BF16 in 2D."""
     got = {k: v for k, v in spills.items() if k.startswith("k_push_final<")}
-    assert len(got) == 72
+    assert len(got) == 56
     for name, n in got.items():
-        if name.endswith(", 8>"):
-            continue
-        assert n <= (4 if name == "k_push_final<2, double, true, 1024, 5>" else 0), (name, n)
+        allowed = 5 if name.startswith("k_push_final<2, bf16s, false") else 0
+        assert n <= allowed or name.endswith(", 8>"), (name, n)
