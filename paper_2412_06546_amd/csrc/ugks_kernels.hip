@@ -1980,13 +1980,19 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(D == 3 ? 6 :
 // set-up that every workgroup repeats, so a share may be a single iteration:
 // with at least four iterations a share, a colour launch of a 2,197-cell
 // channel (1,331 velocities) took 24.2 us and now takes 13.0, one of a
-// 4,096-cell box with 2,145 scattered velocities 32.8 and now 23.3.
+// 4,096-cell box with 2,145 scattered velocities 32.8 and now 23.3 (with a fill
+// of 8,192).  Where the tables that every share fills are long (`tables`
+// entries in all), a share is at least as long as they are worth: 16,200 cells
+// in 2D x 400 velocities with 800 coordinate values, in colours, 0.61 ms a step
+// in shares of one iteration, 0.45 unsplit; 1,800 cells 0.138 and 0.124; 512
+// in 3D x 285, classes of about 40, 0.242 and 0.262: those stay split.
 constexpr int kPushFill = 4096;
-inline int push_ksplit(int n, int kn, int bs)
+inline int push_ksplit(int n, int kn, int bs, int tables)
 {
     const int iters = (kn + bs - 1) / bs;  // velocity iterations of one workgroup
     const int split = std::max(1, std::min(iters, (kPushFill + n - 1) / n));
-    const int per = (iters + split - 1) / split;
+    const int least = n >= 128 ? std::min(iters, (tables + 8 * bs - 1) / (8 * bs)) : 1;
+    const int per = std::max((iters + split - 1) / split, least);
     return per * bs;
 }
 
@@ -3240,7 +3246,7 @@ hipError_t push_t(const Params &p, void *fv, void *av, bool need_base, const int
             }
         }
         const unsigned g = (unsigned)sweep_grid(n);
-        const int ks = push_ksplit(n, p.nv, BS);
+        const int ks = push_ksplit(n, p.nv, BS, TENSOR ? (MF + 1) * p.ntab : 0);
         const dim3 grid(g, (unsigned)((p.nv + ks - 1) / ks));
         if constexpr (TENSOR)
             hipLaunchKernelGGL((k_push_pf<D, FT, BS>), grid, dim3(BS), tab + red, s, p, fin, acc, cells + coff[c], n, 0,
@@ -3287,7 +3293,7 @@ hipError_t push_inplace_t(const Params &p, void *fv, const int *cells, const int
             const int n = coff[c + 1] - coff[c];
             if (n <= 0) continue;
             const unsigned g = (unsigned)sweep_grid(n);
-            const int ks = push_ksplit(n, cn, BS);
+            const int ks = push_ksplit(n, cn, BS, TENSOR ? (MF + 1) * p.ntab : 0);
             const dim3 grid(g, (unsigned)((cn + ks - 1) / ks));
             if constexpr (TENSOR)
                 hipLaunchKernelGGL((k_push_pf<D, FT, BS>), grid, dim3(BS), tab + red, s, p, f, ring, cells + coff[c], n,

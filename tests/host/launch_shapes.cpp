@@ -134,6 +134,26 @@ void final_forms()
     g_launches.clear();
 }
 
+// A small class of cells is split down to one iteration a share, unless the
+// tables that every share fills are long.
+void cell_shares()
+{
+    auto shares = [](int dim, int cells, int nv, int ntab) {
+        const int all[2] = {0, cells};
+        g_launches.clear();
+        (void)ugx::launch_push_step(params(dim, 1, cells, nv, ntab, 0), nullptr, nullptr, false, nullptr, all, 1, 0, nullptr, 0,
+                                    nullptr);
+        expect(g_launches.size() == 2, "a class and the final kernel");
+        return (int)g_launches[0].grid.y;
+    };
+    expect(shares(3, 157, 1331, 33) == 6 && shares(3, 273, 2145, 0) == 9 && shares(2, 100, 3600, 120) == 15,
+           "a class of few cells is not split");
+    expect(shares(2, 1350, 400, 800) == 1 && shares(3, 500, 290, 870) == 1 && shares(2, 128, 4096, 800) == 8,
+           "shares shorter than their tables");
+    expect(shares(3, 40, 285, 855) == 2, "a class of very few cells is split all the same");
+    g_launches.clear();
+}
+
 // Bricks only where the velocities fill the lanes, and a launch of few bricks
 // on as many workgroups as their velocity iterations give.
 void brick_launches()
@@ -318,6 +338,7 @@ int main()
 {
     largest_meshes();
     final_forms();
+    cell_shares();
     brick_launches();
     colours_write_apart();
     read_out();
