@@ -596,9 +596,10 @@ int nchunk_of(int chunk, int nv) { return (nv + chunk - 1) / chunk; }
 // whether a handle sweeps by pushing each face flux once (else gathering).
 // Automatic choice: push, except for 2D with FP64 f in two buffers, where
 // gathering is faster on MI355X (2D hypersonic cylinder, 20,000 cells x
-// 3,600 velocities: 2.6 against 3.8 ms per step; FP32 f 2.4 push against 3.2
-// gather; the 3D lifting body on 107,118 cells 15.6 push against 25.3 gather
-// in FP64).
+// 3,600 velocities: 2.65 against 3.71 ms per step; the 3D lifting body on
+// 107,118 cells 15.6 push against 25.3 gather in FP64).  FP32 f in 2D was
+// faster by push when the line was drawn (2.7 against 2.9) and is not now (2.36
+// against 2.16); it stays, so that a default run keeps its bits.
 // BF16 f pushes only when asked: its accumulator (the second buffer, or the
 // ring in place) holds FP32 stage-1 sums, 2 more bytes per value.
 bool asks_push(const ugks_gas_t *gas) { return gas->sweep == UGKS_SWEEP_PUSH || gas->sweep == UGKS_SWEEP_PUSH_UNORDERED; }
